@@ -52,7 +52,50 @@ struct KArgs {
   // temperature dependence of the opacity: (T/T_ref)^t_exp [1 - e^{-x}]^stim
   double t_exp, itref;  // itref = 1/T_ref
   int32_t stim, pad;
+  // the workgroups' ranges of cells (block_range; single-table kernel only)
+  int64_t region;     // cells per region
+  int64_t first;      // cells of a region that its first workgroup takes
+  int32_t regions;    // regions, one workgroup of each per round
+  int32_t least;      // least cells per workgroup of the later rounds
 };
+
+// Cells are dealt to workgroups by the line (a line of 128 B holds 16 cells of
+// a row).
+constexpr int64_t kLineCells = 16;
+
+// Cells that the workgroups of round r take of their regions, given the count
+// of round r - 1 (r = 0: a.first): half, in whole lines, and at least a.least.
+__host__ __device__ inline int64_t next_count(int64_t count, int32_t least) {
+  const int64_t half = (count / 2 + kLineCells - 1) / kLineCells * kLineCells;
+  return half < least ? least : half;
+}
+
+// The cells [lo, hi) of workgroup b.  The cells are cut into a.regions regions
+// (as many as workgroups fit the chip at once), and workgroups are numbered in
+// rounds of one workgroup per region: the first takes the first half of its
+// region, the next one half of what is left, and so on.  The hardware starts
+// workgroup after workgroup in this order as earlier ones end, so a compute
+// unit that runs ahead takes more of the later, shorter ranges and all end
+// together.  One equal range per workgroup left the chip a fifth empty on
+// average, since a SIMD favours its oldest waves: at 2^21 cells x 64 groups the
+// workgroups ended between 11.7 and 19.8 ms, and the launch took 20.2 ms
+// against 17.8 ms (2^21 x 16: 4.98 -> 3.94 ms; 2^24 x 64: 153 -> 138 ms).
+// Every round spreads over all regions, because rows are a power of two apart
+// in the common grids: workgroups close together in the rows' index then
+// compete for the same sets of the caches (2^24 x 64 with the rounds laid end
+// to end instead: 156 ms).
+__host__ __device__ inline void block_range(const KArgs& a, int64_t b, int64_t& lo,
+                                            int64_t& hi) {
+  int64_t off = 0, count = a.first;
+  while (b >= a.regions) {
+    b -= a.regions;
+    off += count;
+    count = next_count(count, a.least);
+  }
+  const int64_t end = (b + 1) * a.region < a.n ? (b + 1) * a.region : a.n;
+  lo = b * a.region + off < end ? b * a.region + off : end;
+  hi = lo + count < end ? lo + count : end;
+}
 
 // Fill the derived constants of a (host side); outputs left NULL are the
 // inputs (an update in place).

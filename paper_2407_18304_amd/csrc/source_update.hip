@@ -127,6 +127,35 @@ static int num_cus() {
   return cus;
 }
 
+// The workgroups of a launch and their ranges (block_range): in_flight cells
+// are in flight in a workgroup, resident workgroups on the chip.  Ranges do
+// not get shorter than twice the cells in flight, which would be mostly
+// draining; cells for fewer than four of those per resident workgroup are
+// dealt in one round of equal ranges.  A region is an odd number of lines long,
+// so that the regions of a power-of-two grid start at different sets of the
+// caches (2^21 cells x 16 groups 4.60 -> 3.97 ms).
+static int64_t plan_blocks(KArgs& a, int64_t in_flight, int64_t resident) {
+  const int64_t n = a.n;
+  a.least = (int32_t)(2 * in_flight);
+  if (n <= 4 * a.least * resident) {
+    const int64_t most = (n + in_flight - 1) / in_flight;
+    const int64_t blocks = most < resident ? most : resident;
+    a.region = a.first = (n + blocks - 1) / blocks;
+    a.regions = INT32_MAX;
+    return (n + a.region - 1) / a.region;
+  }
+  const int64_t lines = (n + kLineCells * resident - 1) / (kLineCells * resident);
+  a.region = kLineCells * (lines | 1);
+  a.regions = (int32_t)resident;
+  a.first = next_count(a.region, a.least);
+  int64_t rounds = 0;
+  for (int64_t off = 0, count = a.first; off < a.region; ++rounds) {
+    off += count;
+    count = next_count(count, a.least);
+  }
+  return rounds * resident;
+}
+
 }  // namespace mgrhd
 
 using namespace mgrhd;
@@ -279,13 +308,10 @@ int mgrhd_source_update(double* E_g, double* F_g, const double* rho, double* e_g
   a.stim = op->stim;
   set_derived(a);
 
-  // persistent grid: one resident wave of workgroups, never more workgroups
-  // than there are cell groups to fill them
-  const int64_t needed = (n_cells * var->lpc + kBlock - 1) / kBlock;
   const int full = var->lpc * var->g == ng ? 1 : 0;  // every slot holds a group
   const int64_t resident =
       (int64_t)num_cus() * resident_blocks(var, td, full, op->mean_mode);
-  const int64_t blocks = needed < resident ? needed : resident;
+  const int64_t blocks = plan_blocks(a, kBlock / var->lpc, resident);
   hipLaunchKernelGGL(var->fn[td][full][op->mean_mode], dim3((unsigned)blocks), dim3(kBlock), 0,
                      (hipStream_t)stream, a);
   const hipError_t err = hipGetLastError();
