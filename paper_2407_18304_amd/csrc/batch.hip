@@ -4,13 +4,14 @@
 //
 // Work list: the patches are cut into items of at most `chunk` cells, ordered
 // by decreasing group count (the costliest work first, so the tail of the
-// launch is made of cheap items).  A wave takes the next item with one atomic
-// increment of a global counter, stages that patch's tables in its own LDS
-// slot, sets its lane count per cell to the next power of two >= N_g/G, and
-// runs the same per-cell state machine as the single-table kernel (cell
-// groups refill from the item's cells as their cells finish).  A tiny kernel
-// clears the counter before the persistent kernel, so the pair can be
-// captured in a hipGraph and replayed.
+// launch is made of cheap items).  By default one workgroup runs one item and
+// the hardware hands out the items (k_batch_items).  In the other scopes a wave
+// or a workgroup takes the next item with one atomic increment of a global
+// counter, stages that patch's tables in its LDS slot, sets its lane count per
+// cell to the next power of two >= N_g/G, and runs the same per-cell state
+// machine as the single-table kernel (cell groups refill from the item's cells
+// as their cells finish); a tiny kernel clears the counter before that, so the
+// pair can be captured in a hipGraph and replayed.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -22,7 +23,7 @@
 
 #include "../../include/mgrhd.h"
 #include "batch_infer.hpp"
-#include "solver_device.hpp"
+#include "solver_kernel.hpp"
 
 namespace mgrhd {
 
@@ -162,10 +163,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch(BatchArgs b) {
 // take the item's cells through an LDS counter, so the cells in flight in a
 // workgroup share the cache lines of every SoA row.  Waves that run out of
 // cells wait at the item's end for the others.
-// WPE: waves per SIMD the register allocation must allow (LDS allows 3 at 2
-// groups per lane; at 3 a few registers spill, at 2 none do).
-template <int G, int MODE, int NGM, int WPE>
-__global__ __launch_bounds__(kBlock, WPE) void k_batch_wg(BatchArgs b) {
+template <int G, int MODE, int NGM>
+__global__ __launch_bounds__(kBlock, 2) void k_batch_wg(BatchArgs b) {
   static_assert(G * kWave >= NGM, "a wave holds the widest patch");
   __shared__ Tables<NGM> tab;
   __shared__ int item_s, taken;
@@ -206,27 +205,94 @@ __global__ __launch_bounds__(kBlock, WPE) void k_batch_wg(BatchArgs b) {
   }
 }
 
+// One workgroup per item (scope 1 at 2 groups per lane), started by the
+// hardware as earlier ones end.  The state machine is the single-table
+// kernel's for the item's lane count; FULL: every item's N_g fills its lanes,
+// which leaves four waves per SIMD (k_source_update).  The patch's constants
+// are read where they are used (held in scalar registers they spilled 30 of
+// them in each state machine, 1% slower).  LDS is dynamic, as much as the
+// widest item of the launch needs.  Bound by the vector ALU as the
+// single-table kernel.  Taking items from a counter instead (k_batch_wg) asks
+// for an LDS slot for 128 groups, three workgroups per CU, and waits at every
+// item's end for the last of its cells: 24 patches of 1.3e6 cells 8.64 -> 8.04
+// ms, 12 patches 3.48 -> 2.79 ms, 6 patches of 3e5 cells 1.41 -> 0.57 ms.
+template <int G, int LPC, int MODE, bool FULL>
+__device__ __forceinline__ void run_item_block(const KArgs& a, KArgsRef ap, const Item& item,
+                                               unsigned char* lds) {
+  run_block<G, LPC, MODE, false, FULL>(a, ap, item.c0, item.c1, *(BlockLds<G, LPC, true>*)lds);
+}
+
+template <int G, int MODE, bool FULL>
+__global__ __launch_bounds__(kBlock, FULL ? 4 : 3) void k_batch_items(const KArgs* patches,
+                                                                      const Item* items) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char batch_lds[];
+  typedef const Item __attribute__((address_space(4)))* ItemRef;
+  const ItemRef ip = (ItemRef)(items + blockIdx.x);
+  const Item item{ip->patch, 0, ip->c0, ip->c1};
+  const KArgsRef ap = (KArgsRef)(patches + item.patch);
+  KArgs a;
+  __builtin_memcpy(&a, (const KArgs*)ap, sizeof(KArgs));
+  if (a.ng <= G)
+    run_item_block<G, 1, MODE, FULL>(a, ap, item, batch_lds);
+  else if (a.ng <= 2 * G)
+    run_item_block<G, 2, MODE, FULL>(a, ap, item, batch_lds);
+  else if (a.ng <= 4 * G)
+    run_item_block<G, 4, MODE, FULL>(a, ap, item, batch_lds);
+  else if (a.ng <= 8 * G)
+    run_item_block<G, 8, MODE, FULL>(a, ap, item, batch_lds);
+  else if (a.ng <= 16 * G)
+    run_item_block<G, 16, MODE, FULL>(a, ap, item, batch_lds);
+  else if (a.ng <= 32 * G)
+    run_item_block<G, 32, MODE, FULL>(a, ap, item, batch_lds);
+  else
+    run_item_block<G, 64, MODE, FULL>(a, ap, item, batch_lds);
+}
+
+// Lanes per cell of N_g groups at 2 groups per lane, and the LDS of a
+// workgroup of k_batch_items with that many.
+static int item_lanes(int ng) {
+  int lpc = 1;
+  while (lpc * 2 < ng) lpc <<= 1;
+  return lpc;
+}
+static size_t item_lds(int lpc) {
+  switch (lpc) {
+    case 1: return sizeof(BlockLds<2, 1>);
+    case 2: return sizeof(BlockLds<2, 2>);
+    case 4: return sizeof(BlockLds<2, 4>);
+    case 8: return sizeof(BlockLds<2, 8>);
+    case 16: return sizeof(BlockLds<2, 16>);
+    case 32: return sizeof(BlockLds<2, 32>);
+    default: return sizeof(BlockLds<2, 64>);
+  }
+}
+
+using ItemsFn = void (*)(const KArgs*, const Item*);
+static ItemsFn items_fn(int mode, bool full) {
+  static const ItemsFn fn[2][3] = {
+      {k_batch_items<2, MGRHD_MEAN_PC, false>, k_batch_items<2, MGRHD_MEAN_PPL_FIXED, false>,
+       k_batch_items<2, MGRHD_MEAN_PPL_FREE, false>},
+      {k_batch_items<2, MGRHD_MEAN_PC, true>, k_batch_items<2, MGRHD_MEAN_PPL_FIXED, true>,
+       k_batch_items<2, MGRHD_MEAN_PPL_FREE, true>}};
+  return fn[full ? 1 : 0][mode];
+}
+
 using BatchFn = void (*)(BatchArgs);
 // the kernel for g groups per lane, mean mode, and items per wave (scope 0) or
-// per workgroup (scope 1: register budget for 3 waves per SIMD at 2 groups
-// per lane; scope 2: for 2 waves)
+// per workgroup (scope 2, and scope 1 at 4 groups per lane)
 static BatchFn batch_fn(int g, int mode, int scope) {
   static const BatchFn wave[2][3] = {
       {k_batch<2, MGRHD_MEAN_PC, kBatchNGM>, k_batch<2, MGRHD_MEAN_PPL_FIXED, kBatchNGM>,
        k_batch<2, MGRHD_MEAN_PPL_FREE, kBatchNGM>},
       {k_batch<4, MGRHD_MEAN_PC, kBatchNGM>, k_batch<4, MGRHD_MEAN_PPL_FIXED, kBatchNGM>,
        k_batch<4, MGRHD_MEAN_PPL_FREE, kBatchNGM>}};
-  static const BatchFn wg3[3] = {k_batch_wg<2, MGRHD_MEAN_PC, kBatchNGM, 3>,
-                                 k_batch_wg<2, MGRHD_MEAN_PPL_FIXED, kBatchNGM, 3>,
-                                 k_batch_wg<2, MGRHD_MEAN_PPL_FREE, kBatchNGM, 3>};
   static const BatchFn wg2[2][3] = {
-      {k_batch_wg<2, MGRHD_MEAN_PC, kBatchNGM, 2>, k_batch_wg<2, MGRHD_MEAN_PPL_FIXED, kBatchNGM, 2>,
-       k_batch_wg<2, MGRHD_MEAN_PPL_FREE, kBatchNGM, 2>},
-      {k_batch_wg<4, MGRHD_MEAN_PC, kBatchNGM, 2>, k_batch_wg<4, MGRHD_MEAN_PPL_FIXED, kBatchNGM, 2>,
-       k_batch_wg<4, MGRHD_MEAN_PPL_FREE, kBatchNGM, 2>}};
+      {k_batch_wg<2, MGRHD_MEAN_PC, kBatchNGM>, k_batch_wg<2, MGRHD_MEAN_PPL_FIXED, kBatchNGM>,
+       k_batch_wg<2, MGRHD_MEAN_PPL_FREE, kBatchNGM>},
+      {k_batch_wg<4, MGRHD_MEAN_PC, kBatchNGM>, k_batch_wg<4, MGRHD_MEAN_PPL_FIXED, kBatchNGM>,
+       k_batch_wg<4, MGRHD_MEAN_PPL_FREE, kBatchNGM>}};
   const int gi = g == 4 ? 1 : 0;
   if (scope == 0) return wave[gi][mode];
-  if (scope == 1 && g == 2) return wg3[mode];
   return wg2[gi][mode];
 }
 
@@ -250,8 +316,12 @@ struct mgrhd_batch {
   int32_t blocks_per_cu = 0;  // 0 = all resident
   int64_t chunk = 256;
   bool items_dirty = true;
+  // items of patches whose N_g fills its lanes at 2 groups per lane, the first
+  // of the work list; LDS of the widest such item and of the widest other
+  int64_t n_full = 0;
+  size_t lds_full = 0, lds_rest = 0;
   // [first, last) item of each group count (the work list is sorted by
-  // decreasing N_g), rebuilt with the work list
+  // decreasing N_g among the full and among the others), rebuilt with it
   std::vector<std::pair<int32_t, std::pair<int64_t, int64_t>>> ng_items;
   // warm-start networks attached per group count (inference enqueued before
   // the solve)
@@ -267,22 +337,66 @@ struct mgrhd_batch {
   hipGraphExec_t exec = nullptr;
 };
 
+static int device_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      cus < 1)
+    cus = 256;
+  return cus;
+}
+
 static int build_items(mgrhd_batch* bt) {
   std::vector<Item> items;
   std::vector<int32_t> order(bt->n_patches);
   for (int32_t p = 0; p < bt->n_patches; ++p) order[p] = p;
+  auto full = [&](int32_t p) {
+    return 2 * item_lanes(bt->h_patches[p].ng) == bt->h_patches[p].ng;
+  };
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+    if (full(x) != full(y)) return full(x);
     return bt->h_patches[x].ng > bt->h_patches[y].ng;
   });
   bt->ng_items.clear();
+  bt->n_full = 0;
+  bt->lds_full = bt->lds_rest = 0;
+  // With a workgroup per item (k_batch_items) the length of an item counts in
+  // rounds of the cells that a workgroup holds at once, not in cells: as many
+  // rounds for a narrow patch as for a wide one, and, as the hardware starts
+  // item after item, half of what the launch has left for each resident
+  // workgroup, so that all end together (block_range).  Measured: 24 patches
+  // of 1.3e6 cells 8.29 ms with 256 cells per item, 2.4 ms of it the last
+  // items of 64 groups.
+  const bool rounds = bt->scope == 1 && bt->groups_per_lane == 2;
+  constexpr int64_t kLeastRounds = 2;
+  auto in_flight = [](int32_t ng) { return (int64_t)(kBlock / item_lanes(ng)); };
+  int64_t left[2] = {0, 0};  // rounds left of the full items and of the others
+  for (int32_t p : order) {
+    const KArgs& a = bt->h_patches[p];
+    left[full(p)] += (a.n + in_flight(a.ng) - 1) / in_flight(a.ng);
+  }
+  const int64_t resident = (int64_t)device_cus() * 4;
   for (int32_t p : order) {
     const int64_t n = bt->h_patches[p].n;
     const int32_t ng = bt->h_patches[p].ng;
     if (bt->ng_items.empty() || bt->ng_items.back().first != ng)
       bt->ng_items.push_back({ng, {(int64_t)items.size(), (int64_t)items.size()}});
-    for (int64_t c0 = 0; c0 < n; c0 += bt->chunk)
-      items.push_back(Item{p, 0, c0, std::min(n, c0 + bt->chunk)});
+    for (int64_t c0 = 0; c0 < n;) {
+      int64_t cells = bt->chunk;
+      if (rounds) {
+        const int64_t r = std::max(left[full(p)] / (2 * resident), kLeastRounds);
+        cells = std::min(r * in_flight(ng),
+                         std::max<int64_t>(bt->chunk * 32 / item_lanes(ng), 1));
+        left[full(p)] -= (std::min(cells, n - c0) + in_flight(ng) - 1) / in_flight(ng);
+      }
+      const int64_t c1 = std::min(n, c0 + cells);
+      items.push_back(Item{p, 0, c0, c1});
+      c0 = c1;
+    }
     bt->ng_items.back().second.second = (int64_t)items.size();
+    size_t& lds = full(p) ? bt->lds_full : bt->lds_rest;
+    lds = std::max(lds, item_lds(item_lanes(ng)));
+    if (full(p)) bt->n_full = (int64_t)items.size();
   }
   if (bt->d_items) (void)hipFree(bt->d_items);
   bt->d_items = nullptr;
@@ -426,9 +540,10 @@ int mgrhd_batch_set_tuning(mgrhd_batch* bt, int32_t groups_per_lane, int32_t blo
   const bool changed = groups_per_lane != bt->groups_per_lane ||
                        blocks_per_cu != bt->blocks_per_cu || chunk_cells != bt->chunk;
   if (changed) drop_graph(bt);
+  const bool recut = chunk_cells != bt->chunk || groups_per_lane != bt->groups_per_lane;
   bt->groups_per_lane = groups_per_lane;
   bt->blocks_per_cu = blocks_per_cu;
-  if (chunk_cells != bt->chunk) {
+  if (recut) {
     // the work list is rebuilt here, never inside run / capture / launch
     bt->chunk = chunk_cells;
     bt->items_dirty = true;
@@ -443,6 +558,8 @@ int mgrhd_batch_set_item_scope(mgrhd_batch* bt, int32_t per_workgroup) {
   if (per_workgroup != bt->scope) {
     bt->scope = per_workgroup;
     drop_graph(bt);
+    bt->items_dirty = true;
+    return build_items(bt);  // the items of scope 1 are cut by rounds
   }
   return 0;
 }
@@ -473,21 +590,43 @@ static int enqueue_infer(mgrhd_batch* bt, hipStream_t stream) {
   return 0;
 }
 
+// One workgroup per item of [lo, hi).  blocks_per_cu caps the workgroups that
+// a CU holds at once through the LDS that each asks for.
+static int enqueue_items(const mgrhd_batch* bt, hipStream_t stream, bool full, int64_t lo,
+                         int64_t hi) {
+  if (lo == hi) return 0;
+  constexpr size_t kCuLds = 160 * 1024, kLaunchLds = 64 * 1024;
+  const ItemsFn fn = items_fn(bt->mode, full);
+  size_t lds = full ? bt->lds_full : bt->lds_rest;
+  if (bt->blocks_per_cu > 0) {
+    const size_t share = kCuLds / (size_t)bt->blocks_per_cu;
+    const size_t pad = share / 1024 * 1024;
+    if (pad > lds) lds = pad;
+  }
+  if (lds > kLaunchLds &&
+      hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                          (int)kCuLds) != hipSuccess)
+    return MGRHD_E_DEVICE;
+  hipLaunchKernelGGL(fn, dim3((unsigned)(hi - lo)), dim3(kBlock), lds, stream,
+                     (const KArgs*)bt->d_patches, (const Item*)(bt->d_items + lo));
+  const hipError_t err = hipGetLastError();
+  return err == hipSuccess ? 0 : (int)err;
+}
+
 static int enqueue(mgrhd_batch* bt, hipStream_t stream) {
   if (bt->items_dirty) return MGRHD_E_DEVICE;  // the last rebuild of the work list failed
   if (bt->n_items == 0) return 0;
   if (const int rc = enqueue_infer(bt, stream)) return rc;
+  if (bt->scope == 1 && bt->groups_per_lane == 2) {
+    const int rc = enqueue_items(bt, stream, true, 0, bt->n_full);
+    return rc ? rc : enqueue_items(bt, stream, false, bt->n_full, bt->n_items);
+  }
   BatchFn fn = batch_fn(bt->groups_per_lane, bt->mode, bt->scope);
   int nb = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kBlock, 0) != hipSuccess || nb < 1)
     nb = 1;
   if (bt->blocks_per_cu > 0 && bt->blocks_per_cu < nb) nb = bt->blocks_per_cu;
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      cus < 1)
-    cus = 256;
-  int64_t blocks = (int64_t)cus * nb;
+  int64_t blocks = (int64_t)device_cus() * nb;
   // never more takers than items: waves (scope 0) or workgroups (scope 1)
   if (bt->scope) {
     if (blocks > bt->n_items) blocks = bt->n_items;
@@ -693,10 +832,12 @@ int mgrhd_batch_tune(mgrhd_batch* bt, mgrhd_stream_t stream) {
   for (const TuneCandidate& c : kTuneCandidates) {
     if (rc) break;
     if (bt->max_groups > c.groups_per_lane * 64) continue;
+    const bool recut = c.chunk != tmp.chunk || c.scope != tmp.scope ||
+                       c.groups_per_lane != tmp.groups_per_lane || tmp.items_dirty;
     tmp.groups_per_lane = c.groups_per_lane;
     tmp.scope = c.scope;
     tmp.blocks_per_cu = bt->blocks_per_cu;
-    if (c.chunk != tmp.chunk || tmp.items_dirty) {
+    if (recut) {
       tmp.chunk = c.chunk;
       if (hipStreamSynchronize(st) != hipSuccess) { rc = MGRHD_E_DEVICE; break; }
       if ((rc = build_items(&tmp)) != 0) break;

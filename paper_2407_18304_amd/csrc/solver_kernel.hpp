@@ -10,31 +10,29 @@
 
 namespace mgrhd {
 
-// TD: the opacity depends on temperature (evaluated at every iterate).
-// FULL: N_g = LPC * G (the launcher checks), every slot holds a group.
-// Without the per-slot checks the FULL kernels of two groups per lane fit the
-// 128 registers of four waves per SIMD, whatever the variant asks for (2^21
-// cells x 16 groups 4.35 -> 4.00 ms, PPL-free 5% faster; with the checks they
-// would spill: 11 groups 1.19 -> 1.47 ms).
-template <int G, int LPC, int MODE, int WPE, bool TD, bool FULL>
-__global__ __launch_bounds__(kBlock, FULL && G == 2 && WPE < 4 ? 4 : WPE) void k_source_update(
-    KArgs a) {
-  constexpr int NGM = G * LPC;
-  __shared__ Tables<NGM> tab;
-  using LS = LaneStore<G, true, kBlock / LPC>;
-  __shared__ double lane_lds[LS::kSlots * kBlock];
-  __shared__ double cell_lds[LS::kCellWords];
-  // the arguments as the device reads them in place (a is the only argument)
-  const KArgsRef ap = (KArgsRef)__builtin_amdgcn_kernarg_segment_ptr();
-  const LS ls{lane_lds + threadIdx.x, cell_lds, ap};
-  __shared__ int taken;  // cells of this workgroup's range handed out so far
-  if (threadIdx.x == 0) taken = 0;
-  const bool table_ok = stage_tables<NGM, MODE>(a, tab);  // (its barriers publish `taken`)
+// LDS of one workgroup of the state machine with LPC lanes per cell: the group
+// tables, the per-lane slots, the per-cell area, and the cells of the
+// workgroup's range handed out so far.  AT_USE: LaneStore's CONST_AT_USE.
+template <int G, int LPC, bool AT_USE = false>
+struct BlockLds {
+  using LS = LaneStore<G, true, kBlock / LPC, AT_USE>;
+  Tables<G * LPC> tab;
+  double lane[LS::kSlots * kBlock];
+  double cell[LS::kCellWords];
+  int taken;
+};
 
-  const int lane = threadIdx.x % kWave;
-  // each workgroup owns a contiguous range of cells, shared by its waves
-  int64_t lo, hi;
-  block_range(a, blockIdx.x, lo, hi);
+// The cells [lo, hi) of one state by this workgroup: its tables staged, the
+// cells shared by its waves through the counter in LDS.  ap: the argument
+// block that a was read from.
+template <int G, int LPC, int MODE, bool TD, bool FULL, bool AT_USE>
+__device__ __forceinline__ void run_block(const KArgs& a, KArgsRef ap, int64_t lo, int64_t hi,
+                                          BlockLds<G, LPC, AT_USE>& lds) {
+  constexpr int NGM = G * LPC;
+  using LS = typename BlockLds<G, LPC, AT_USE>::LS;
+  const LS ls{lds.lane + threadIdx.x, lds.cell, ap};
+  if (threadIdx.x == 0) lds.taken = 0;
+  const bool table_ok = stage_tables<NGM, MODE>(a, lds.tab);  // (its barriers publish `taken`)
 
   if (!table_ok) {
     // the table is unusable: report every cell of this workgroup's range
@@ -49,7 +47,26 @@ __global__ __launch_bounds__(kBlock, FULL && G == 2 && WPE < 4 ? 4 : WPE) void k
     return;
   }
 
-  run_cells<G, LPC, MODE, NGM, TD, FULL>(a, tab, ls, lane, BlockQueue{&taken, lo, hi});
+  run_cells<G, LPC, MODE, NGM, TD, FULL>(a, lds.tab, ls, threadIdx.x % kWave,
+                                         BlockQueue{&lds.taken, lo, hi});
+}
+
+// TD: the opacity depends on temperature (evaluated at every iterate).
+// FULL: N_g = LPC * G (the launcher checks), every slot holds a group.
+// Without the per-slot checks the FULL kernels of two groups per lane fit the
+// 128 registers of four waves per SIMD, whatever the variant asks for (2^21
+// cells x 16 groups 4.35 -> 4.00 ms, PPL-free 5% faster; with the checks they
+// would spill: 11 groups 1.19 -> 1.47 ms).
+template <int G, int LPC, int MODE, int WPE, bool TD, bool FULL>
+__global__ __launch_bounds__(kBlock, FULL && G == 2 && WPE < 4 ? 4 : WPE) void k_source_update(
+    KArgs a) {
+  __shared__ BlockLds<G, LPC> lds;
+  // the arguments as the device reads them in place (a is the only argument)
+  const KArgsRef ap = (KArgsRef)__builtin_amdgcn_kernarg_segment_ptr();
+  // each workgroup owns a contiguous range of cells, shared by its waves
+  int64_t lo, hi;
+  block_range(a, blockIdx.x, lo, hi);
+  run_block<G, LPC, MODE, TD, FULL>(a, ap, lo, hi, lds);
 }
 
 using KernelFn = void (*)(KArgs);

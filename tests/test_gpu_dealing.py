@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2407_18304_amd import mgrhd, synth
+from paper_2407_18304_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 KEYS = ("E_g", "F_g", "e_gas", "v")
@@ -40,3 +41,41 @@ def test_rounds_of_ranges(n):
         for k in KEYS:
             assert torch.equal(got[k], whole[k][..., at]), (k, i)
         assert torch.equal(st, status[at])
+
+
+# patches whose groups fill their lanes (8, 64, 128), that leave lanes empty
+# (1, 7, 65), cut by rounds (256), into single cells' worth of lanes (1) and
+# across several items; a cap on the workgroups per CU down to one
+@pytest.mark.parametrize("chunk", [1, 9, 256])
+@pytest.mark.parametrize("blocks_per_cu", [0, 1, 2, 3])
+def test_items_of_a_workgroup(chunk, blocks_per_cu):
+    sizes = ((64, 700), (1, 300), (8, 513), (65, 70), (7, 1), (128, 33), (3, 2000))
+    layouts, cell0 = [], 0
+    for p, (ng, n) in enumerate(sizes):
+        edges = W.log_edges(1e-3, 1e3, ng)
+        layouts.append(W.PatchLayout(p, n, ng, cell0, edges, edges[:-1] ** -2.0,
+                                     torch.full((ng,), -2.0).double().numpy()))
+        cell0 += n
+    dps = synth.device_patches(layouts)
+    patches = []
+    for dp in dps:
+        out = tuple(torch.full_like(dp.state[k], float("nan")) for k in KEYS)
+        patches.append(dict(dp.state, edges=dp.tables["edges"], chi_lo=dp.tables["chi_lo"],
+                            alpha_chi=dp.tables["alpha"], kappa_scale=dp.kappa, dt=dp.dt,
+                            c_hat=dp.c_hat, out=out,
+                            status=torch.full((dp.layout.n,), -7, dtype=torch.int32,
+                                              device="cuda")))
+    b = mgrhd.Batch(patches, polish=1, c_v=1.5, **W.UNITS["patches"])
+    b.set_tuning(2, blocks_per_cu, chunk)
+    b.run()
+    torch.cuda.synchronize()
+    for dp, q in zip(dps, patches):
+        want, status = _update(dp.state, dp.tables, dp.kappa,
+                               {k: v for k, v in dp.consts().items()})
+        assert torch.equal(q["status"], status)
+        for k, got in zip(KEYS, q["out"]):
+            # the same arithmetic, in a kernel that may contract it differently
+            err = (got - want[k]).abs() / want[k].abs().clamp_min(1e-300)
+            scale = want[k].abs().max()
+            ok = (err < 1e-10) | ((got - want[k]).abs() < 1e-14 * scale)
+            assert bool(ok.all()), (dp.layout.ng, k, float(err.max()))
