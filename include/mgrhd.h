@@ -184,7 +184,9 @@ int mgrhd_source_update(double* E_g, double* F_g, const double* rho, double* e_g
                         const mgrhd_opacity_params* opacity, double dt, double c_hat,
                         mgrhd_stream_t stream, const mgrhd_options* opt);
 
-/* Kernel variant used for a given group count: lanes per cell, groups per
+/* Kernel variant used for a given group count (launches too small to fill the
+ * GPU, and most PPL-free ones, may split a cell over one lane per group unless
+ * mgrhd_set_variant has been called for that count): lanes per cell, groups per
  * lane and the register budget, given as the minimum resident waves per SIMD
  * it is compiled for (more waves: fewer registers per lane).
  * mgrhd_set_variant overrides the built-in choice for n_groups (0, 0, 0

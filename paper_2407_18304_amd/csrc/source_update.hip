@@ -127,6 +127,35 @@ static int num_cus() {
   return cus;
 }
 
+// The variant of a launch of n cells.  A launch that leaves the chip part empty
+// takes as long as its slowest cell, and a lane with one group has half of a
+// step's work: 4096 cells x 4 groups 64.8 -> 48.7 us, 500 x 16 62.3 -> 40.8,
+// 2048 x 64 56.5 -> 46.9.  The lines, in quarters of the lanes that the chip
+// holds at four waves per SIMD:
+// * 3 where the groups fill the lanes (16384 x 16, all of them, 77.9 -> 74.0
+//   us, but 65536 x 4 81.6 -> 87.9) or the opacity depends on temperature (per
+//   cell it costs two more functions in every lane: 50000 x 5 227 -> 244 us);
+// * 8 where they leave lanes of both splits empty, since the kernels with the
+//   per-slot checks hold a third more waves at one group per lane (30011 x 11
+//   103.1 -> 94.6 us, but 125000 x 5 201 -> 213);
+// * PPL-free holds more of them still: 16 where the groups fill the lanes
+//   (62500 x 16 829 -> 706 us, but 125000 x 64 2650 -> 2775), always where they
+//   do not (2^19 x 11 5.18 -> 4.56 ms).
+// A variant set by the caller is kept.
+static Variant* launch_variant(int ng, int mode, bool td, int64_t n) {
+  Variant* v = choose_variant(ng);
+  if (!v || g_override_lpc[ng] || ng > kWave) return v;
+  int lpc = 4;
+  while (lpc < ng) lpc <<= 1;
+  const bool full = v->lpc * v->g == ng;
+  const int64_t quarter = (int64_t)num_cus() * kBlock;
+  int64_t most = 3 * quarter;
+  if (!full && !td) most = 8 * quarter;
+  if (mode == MGRHD_MEAN_PPL_FREE && !td) most = full ? 16 * quarter : INT64_MAX;
+  Variant* one = n <= most / lpc ? find_variant(lpc, 1, 0) : nullptr;
+  return one ? one : v;
+}
+
 // The workgroups of a launch and their ranges (block_range): in_flight cells
 // are in flight in a workgroup, resident workgroups on the chip.  Ranges do
 // not get shorter than twice the cells in flight, which would be mostly
@@ -260,7 +289,7 @@ int mgrhd_source_update(double* E_g, double* F_g, const double* rho, double* e_g
     return MGRHD_E_TABLE;
   const int td = (op->t_exp != 0.0 || op->stim != 0) ? 1 : 0;
 
-  Variant* var = choose_variant(ng);
+  Variant* var = launch_variant(ng, op->mean_mode, td != 0, n_cells);
   if (!var) return MGRHD_E_OPTION;
   link_kernels();
 

@@ -12,7 +12,7 @@ KEYS = ("E_g", "F_g", "e_gas", "v")
 PAD = 64
 
 
-def _update(state, tables, kappa, consts):
+def _update(state, tables, kappa, consts, mode=mgrhd.MEAN_PPL_FIXED):
     n = kappa.numel()
     flat = {k: torch.full((state[k].numel() + PAD,), -7.0, dtype=torch.float64, device="cuda")
             for k in KEYS}
@@ -20,17 +20,35 @@ def _update(state, tables, kappa, consts):
     status = torch.full((n + PAD,), -7, dtype=torch.int32, device="cuda")
     mgrhd.source_update(state["E_g"], state["F_g"], state["rho"], state["e_gas"], state["v"],
                         tables["edges"], tables["chi_lo"], alpha_chi=tables["alpha"],
-                        kappa_scale=kappa, polish=1, status=status[:n], out=out, **consts)
+                        kappa_scale=kappa, polish=1, status=status[:n], out=out,
+                        mean_mode=mode, **consts)
     assert all(bool((flat[k][-PAD:] == -7.0).all()) for k in KEYS)
     assert bool((status[-PAD:] == -7).all())
     return dict(zip(KEYS, out)), status[:n]
+
+
+def _close(got, want, what):
+    """The same arithmetic with sums in another order, or contracted otherwise:
+    the parity bound of each value, or the rounding of the largest."""
+    diff = (got - want).abs()
+    err = diff / want.abs().clamp_min(1e-300)
+    ok = (err < 1e-10) | (diff < 1e-14 * want.abs().max())
+    assert bool(ok.all()), (*what, float(err.max()))
+
+
+@pytest.fixture
+def one_split():
+    """The same split of a cell over lanes whatever the launch's size."""
+    mgrhd.set_variant(64, 32, 2)
+    yield
+    mgrhd.set_variant(64, 0, 0)
 
 
 # 64 groups: 8 cells in flight in a workgroup, up to 1024 workgroups at once,
 # so that several rounds begin beyond 4 x 16 x 1024 cells (fewer where fewer
 # workgroups fit); sizes at that edge, off any multiple, and a power of two
 @pytest.mark.parametrize("n", [49151, 49153, 65535, 65536, 65537, 100003, 131072])
-def test_rounds_of_ranges(n):
+def test_rounds_of_ranges(n, one_split):
     dw = synth.device_workload("config2", n=n)
     whole, status = _update(dw.state, dw.tables, dw.kappa, dw.consts())
     step = 8191
@@ -74,8 +92,29 @@ def test_items_of_a_workgroup(chunk, blocks_per_cu):
                                {k: v for k, v in dp.consts().items()})
         assert torch.equal(q["status"], status)
         for k, got in zip(KEYS, q["out"]):
-            # the same arithmetic, in a kernel that may contract it differently
-            err = (got - want[k]).abs() / want[k].abs().clamp_min(1e-300)
-            scale = want[k].abs().max()
-            ok = (err < 1e-10) | ((got - want[k]).abs() < 1e-14 * scale)
-            assert bool(ok.all()), (dp.layout.ng, k, float(err.max()))
+            _close(got, want[k], (dp.layout.ng, k))
+
+
+# launches around the sizes at which a cell's groups are split over more lanes
+# (three quarters of, and twice, the lanes that 256 compute units
+# hold; PPL-free four times),
+# against a split set for every size: groups that fill the lanes and that do not
+@pytest.mark.parametrize("ng,split,n,mode", [
+    (4, (2, 2), 49152, 1), (4, (2, 2), 49153, 1), (16, (8, 2), 12288, 0),
+    (16, (8, 2), 12289, 0), (64, (32, 2), 3072, 1), (64, (32, 2), 3073, 1), (3, (2, 2), 7, 1),
+    (1, (1, 4), 1, 1), (2, (1, 4), 130, 0), (33, (32, 2), 8192, 1), (33, (32, 2), 8193, 1),
+    (64, (32, 2), 16384, 2), (64, (32, 2), 16385, 2), (23, (16, 2), 5000, 2)])
+def test_split_of_a_small_launch(ng, split, n, mode):
+    edges = W.log_edges(1e-3, 1e3, ng)
+    layout = W.PatchLayout(0, n, ng, 0, edges, edges[:-1] ** -2.0,
+                           torch.full((ng,), -2.0).double().numpy())
+    dp, = synth.device_patches([layout])
+    got, st = _update(dp.state, dp.tables, dp.kappa, dp.consts(), mode)
+    mgrhd.set_variant(ng, *split)
+    try:
+        want, want_st = _update(dp.state, dp.tables, dp.kappa, dp.consts(), mode)
+    finally:
+        mgrhd.set_variant(ng, 0, 0)
+    assert torch.equal(st, want_st)
+    for k in KEYS:
+        _close(got[k], want[k], (ng, n, k))
