@@ -212,19 +212,26 @@ __global__ void k_zero(float* p, int64_t n) {
     p[i] = 0.f;
 }
 
+// One Adam step of parameter i with gradient gi; returns the new parameter.
+__device__ __forceinline__ float adam_update(float* p, float* m, float* v, int64_t i, float gi,
+                                             float lr, float b1, float b2, float eps, float c1,
+                                             float c2) {
+  const float mi = b1 * m[i] + (1.f - b1) * gi;
+  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+  m[i] = mi;
+  v[i] = vi;
+  const float x = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  p[i] = x;
+  return x;
+}
+
 // Adam on FP32 master parameters
 __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
                        float* __restrict__ v, int64_t n, float lr, float b1, float b2, float eps,
                        float c1, float c2) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  }
+       i += (int64_t)gridDim.x * blockDim.x)
+    adam_update(p, m, v, i, g[i], lr, b1, b2, eps, c1, c2);
 }
 
 // ---------------------------------------------------------------------------
@@ -642,20 +649,28 @@ __global__ __launch_bounds__(256, 2) void k_infer_items(InferItemsArgs a) {
   }
 }
 
-// fp32 weights [N x K] -> bf16 [N_pad x K_pad] (zero padded); biases -> fp32 [N_pad]
+// fp32 weights [N x K] -> bf16 [N_pad x K_pad] (zero padded) and, where WT is
+// given, their transpose [K x kt_pad] (its padding stays as it is); biases ->
+// fp32 [N_pad]
 __global__ void k_pack(const float* __restrict__ W, const float* __restrict__ b, int N, int K,
-                       int N_pad, int K_pad, __bf16* __restrict__ Wp, float* __restrict__ bp) {
+                       int N_pad, int K_pad, __bf16* __restrict__ Wp, float* __restrict__ bp,
+                       __bf16* __restrict__ WT, int kt_pad) {
   const int64_t total = (int64_t)N_pad * K_pad;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int nn = (int)(e / K_pad), kk = (int)(e % K_pad);
-    Wp[e] = (__bf16)((nn < N && kk < K) ? W[(int64_t)nn * K + kk] : 0.f);
+    const bool in = nn < N && kk < K;
+    const __bf16 w = (__bf16)(in ? W[(int64_t)nn * K + kk] : 0.f);
+    Wp[e] = w;
+    if (WT && in) WT[(int64_t)kk * kt_pad + nn] = w;
     if (kk == 0) bp[nn] = nn < N ? b[nn] : 0.f;
   }
 }
 
 }  // namespace mlp
 }  // namespace mgrhd
+
+#include "mlp_train.hpp"
 
 using namespace mgrhd::mlp;
 
@@ -669,12 +684,13 @@ struct mgrhd_mlp {
   int64_t n_params = 0;
   int in_dim[kLayers], out_dim[kLayers];
   int64_t w_off[kLayers], b_off[kLayers];
+  void* owned = nullptr;    // params to bpack and wtrans
   float* params = nullptr;  // [n_params] weights (out x in, row-major) then biases
   float* grads = nullptr;
   float* adam_m = nullptr;
   float* adam_v = nullptr;
-  float* act = nullptr;     // H1..H3, Z1..Z3, Y, dY, dH, dZ scratch
   float* loss = nullptr;    // device scalar
+  float* act = nullptr;     // H1..H3, Z1..Z3, Y, dY, dH, dZ scratch; then `partial`
   int64_t step = 0;
   float* H[3];
   float* Zs[3];
@@ -689,6 +705,13 @@ struct mgrhd_mlp {
   int64_t wp_off[kLayers], bp_off[kLayers];
   bool dirty = true;
   bool fp32 = false;  // FP32 operands in the forward and backward products
+  // the three-kernel training pass (128 hidden units, inputs that fit its
+  // tiles): BF16 transposes of the weights, partial sums
+  bool fused = false;
+  __bf16* wtrans = nullptr;
+  float* partial = nullptr;     // [kMaxSplits][n_params] weight gradients
+  int kt_pad[kLayers];
+  int64_t wt_off[kLayers];
 };
 
 static inline dim3 grid1(int64_t n) {
@@ -734,6 +757,15 @@ static void forward(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld_x
                               m->out_dim[3], m->in_dim[3], 1, m->fp32);
 }
 
+// Adam's constants and the bias corrections of step `step`
+static void adam_factors(int64_t step, float& b1, float& b2, float& eps, float& c1, float& c2) {
+  b1 = 0.9f;
+  b2 = 0.999f;
+  eps = 1e-8f;
+  c1 = 1.f - std::pow(b1, (float)step);
+  c2 = 1.f - std::pow(b2, (float)step);
+}
+
 // backward: gradients of mean((Y - T)^2) with respect to all parameters
 static void backward(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld_x, int64_t rows,
                      const float* Tgt) {
@@ -770,6 +802,131 @@ static void backward(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld_
                        rows * (int64_t)ni);
     dOut = dZ;
   }
+}
+
+// The BF16 copies of the weights brought up to date.  In a capture nothing has
+// run yet, so the copies stay marked as old for calls outside the graph.
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
+static void pack_weights(mgrhd_mlp* m, hipStream_t s) {
+  if (!m->dirty) return;
+  for (int l = 0; l < 4; ++l)
+    hipLaunchKernelGGL(k_pack, grid1((int64_t)m->n_pad[l] * m->k_pad[l]), dim3(256), 0, s,
+                       m->params + m->w_off[l], m->params + m->b_off[l], m->out_dim[l],
+                       m->in_dim[l], m->n_pad[l], m->k_pad[l], m->wpack + m->wp_off[l],
+                       m->bpack + m->bp_off[l], m->wtrans ? m->wtrans + m->wt_off[l] : nullptr,
+                       m->kt_pad[l]);
+  m->dirty = capturing(s);
+}
+
+// Gradients of `rows` rows by the three kernels of mlp_train.hpp, into
+// m->grads and m->loss (and loss_out); adam: with the step of rate lr.
+static int train_pass(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld_x, int64_t rows,
+                      const float* Tgt, float* loss_out, bool adam, float lr) {
+  pack_weights(m, s);
+  const int64_t pitch = (rows + kRowTile - 1) / kRowTile * kRowTile;
+  const int64_t row_blocks = pitch / kRowTile;
+  TrainArgs t;
+  std::memset(&t, 0, sizeof(t));
+  t.X = X_fm;
+  t.T = Tgt;
+  t.ldx = ld_x;
+  t.rows = rows;
+  t.pitch = pitch;
+  t.n_in = m->n_in;
+  t.n_out = m->n_out;
+  __bf16* at = (__bf16*)m->act;
+  auto take = [&](int units) {
+    __bf16* p = at;
+    at += (int64_t)units * pitch;
+    return p;
+  };
+  t.XT = take(m->k_pad[0]);
+  for (int l = 0; l < 4; ++l) {
+    t.W[l] = m->wpack + m->wp_off[l];
+    t.WT[l] = m->wtrans + m->wt_off[l];
+    t.b[l] = m->bpack + m->bp_off[l];
+    t.K_pad[l] = m->k_pad[l];
+    t.N_pad[l] = m->n_pad[l];
+    t.kt_pad[l] = m->kt_pad[l];
+    if (l < 3) t.HT[l] = take(kHT);
+    t.dT[l] = take(m->n_pad[l]);
+  }
+  const int bias_width = 3 * kHT + m->n_pad[3];
+  t.bias_part = (float*)at;  // [row tiles][bias_width], then a loss per row tile
+  t.loss_part = t.bias_part + row_blocks * bias_width;
+  t.scale = 1.f / (float)(rows * m->n_out);
+  hipLaunchKernelGGL(k_train_rows, dim3((unsigned)row_blocks), dim3(kRowThreads),
+                     train_lds_bytes(m->k_pad[0], m->kt_pad[3]), s, t);
+
+  DwArgs d;
+  std::memset(&d, 0, sizeof(d));
+  for (int l = 0; l < 4; ++l) {
+    d.A[l] = t.dT[l];
+    d.B[l] = l == 0 ? t.XT : t.HT[l - 1];
+    d.M[l] = m->out_dim[l];
+    d.N[l] = m->in_dim[l];
+    d.M_pad[l] = m->n_pad[l];
+    d.N_pad[l] = m->k_pad[l];
+    d.tiles_n[l] = (d.N[l] + 63) / 64;
+    d.first[l + 1] = d.first[l] + (d.M[l] + 63) / 64 * d.tiles_n[l];
+    d.w_off[l] = m->w_off[l];
+  }
+  // row ranges: some 500 workgroups, ranges of at least 64 rows
+  int64_t splits = std::min<int64_t>(512 / d.first[4], pitch / 64);
+  splits = std::max<int64_t>(1, std::min<int64_t>(splits, kMaxSplits));
+  d.chunk = ((pitch + splits - 1) / splits + 31) / 32 * 32;
+  splits = (pitch + d.chunk - 1) / d.chunk;
+  d.pitch = pitch;
+  d.n_params = m->n_params;
+  d.part = m->partial;
+  hipLaunchKernelGGL(k_train_dw, dim3((unsigned)d.first[4], (unsigned)splits), dim3(256), 0, s, d);
+
+  FinishArgs f;
+  std::memset(&f, 0, sizeof(f));
+  f.part = m->partial;
+  f.bias_part = t.bias_part;
+  f.loss_part = t.loss_part;
+  f.splits = (int)splits;
+  f.row_blocks = (int)row_blocks;
+  f.bias_width = bias_width;
+  f.loss_scale = t.scale;
+  f.loss = m->loss;
+  f.loss_out = loss_out;
+  f.p = m->params;
+  f.g = m->grads;
+  f.m = m->adam_m;
+  f.v = m->adam_v;
+  f.n_params = m->n_params;
+  f.n_weights = m->b_off[0];
+  f.n_weight_blocks = (f.n_weights + 255) / 256;
+  for (int l = 0; l < 4; ++l) {
+    f.w_off[l] = m->w_off[l];
+    f.b_off[l] = m->b_off[l];
+    f.in_dim[l] = m->in_dim[l];
+    f.out_dim[l] = m->out_dim[l];
+    f.K_pad[l] = m->k_pad[l];
+    f.kt_pad[l] = m->kt_pad[l];
+    f.W[l] = m->wpack + m->wp_off[l];
+    f.WT[l] = m->wtrans + m->wt_off[l];
+    f.b[l] = m->bpack + m->bp_off[l];
+  }
+  const unsigned blocks =
+      (unsigned)(f.n_weight_blocks + (m->n_params - f.n_weights + 7) / 8);
+  if (adam) {
+    m->step += 1;
+    adam_factors(m->step, f.b1, f.b2, f.eps, f.c1, f.c2);
+    f.lr = lr;
+    hipLaunchKernelGGL(k_train_finish<true>, dim3(blocks), dim3(256), 0, s, f);
+    m->dirty = capturing(s);  // (the copies are written with the weights)
+  } else {
+    hipLaunchKernelGGL(k_train_finish<false>, dim3(blocks), dim3(256), 0, s, f);
+  }
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? 0 : (int)e;
 }
 
 extern "C" {
@@ -815,8 +972,12 @@ int mgrhd_mlp_create(int32_t n_in, int32_t n_hidden, int32_t n_out, int64_t max_
     for (int64_t k = 0; k < (int64_t)dims[l] * dims[l + 1]; ++k)
       h[m->w_off[l] + k] = (float)((2.0 * next() - 1.0) * lim);
   }
-  const int64_t act = (int64_t)max_rows * (6 * n_hidden + 2 * n_out + 2 * std::max(n_hidden, n_out));
-  int64_t wtot = 0, btot = 0;
+  // (the three-kernel pass keeps its BF16 arrays of whole row tiles and their
+  // sums here: at most 2 (416 + 6 * 128 + 256) + 4 (3 * 128 + 257) / 32 of these
+  // 4104 bytes or more per row)
+  const int64_t act = (max_rows + kRowTile) *
+                      (6 * n_hidden + 2 * n_out + 2 * (int64_t)std::max(n_hidden, n_out));
+  int64_t wtot = 0, btot = 0, ttot = 0;
   for (int l = 0; l < 4; ++l) {
     m->k_pad[l] = (dims[l] + 31) / 32 * 32;
     m->n_pad[l] = (dims[l + 1] + 15) / 16 * 16;
@@ -824,24 +985,44 @@ int mgrhd_mlp_create(int32_t n_in, int32_t n_hidden, int32_t n_out, int64_t max_
     m->bp_off[l] = btot;
     wtot += (int64_t)m->k_pad[l] * m->n_pad[l];
     btot += m->n_pad[l];
+    m->kt_pad[l] = (dims[l + 1] + 31) / 32 * 32;
+    m->wt_off[l] = ttot;
+    ttot += (int64_t)dims[l] * m->kt_pad[l];
   }
-  bool ok = hipMalloc(&m->wpack, sizeof(__bf16) * wtot) == hipSuccess &&
-            hipMalloc(&m->bpack, sizeof(float) * btot) == hipSuccess &&
-            hipMalloc(&m->params, sizeof(float) * off) == hipSuccess &&
-            hipMalloc(&m->grads, sizeof(float) * off) == hipSuccess &&
-            hipMalloc(&m->adam_m, sizeof(float) * off) == hipSuccess &&
-            hipMalloc(&m->adam_v, sizeof(float) * off) == hipSuccess &&
-            hipMalloc(&m->act, sizeof(float) * act) == hipSuccess &&
-            hipMalloc(&m->loss, sizeof(float)) == hipSuccess;
+  m->fused = n_hidden == kHT && m->k_pad[0] <= kMaxKin;
+  // one allocation of what starts at zero (parameters, gradients, moments, the
+  // padded BF16 copies), one of what a pass writes before it reads
+  int64_t bytes = 0;
+  auto place = [&](int64_t count, size_t each) {
+    const int64_t at = bytes;
+    bytes = (bytes + count * (int64_t)each + 255) / 256 * 256;
+    return at;
+  };
+  const int64_t at_params = place(off, sizeof(float)), at_grads = place(off, sizeof(float)),
+                at_m = place(off, sizeof(float)), at_v = place(off, sizeof(float)),
+                at_loss = place(1, sizeof(float)), at_bpack = place(btot, sizeof(float)),
+                at_wpack = place(wtot, sizeof(__bf16)),
+                at_wtrans = m->fused ? place(ttot, sizeof(__bf16)) : 0;
+  const int64_t partial = m->fused ? kMaxSplits * off : 0;
+  unsigned char* base = nullptr;
+  const bool ok =
+      hipMalloc(&m->act, sizeof(float) * (act + partial)) == hipSuccess &&
+      hipMalloc(&m->owned, bytes) == hipSuccess && (base = (unsigned char*)m->owned) &&
+      hipMemset(base, 0, bytes) == hipSuccess &&
+      hipMemcpy(base + at_params, h.data(), sizeof(float) * off, hipMemcpyHostToDevice) ==
+          hipSuccess;
   if (ok) {
-    ok = hipMemcpy(m->params, h.data(), sizeof(float) * off, hipMemcpyHostToDevice) == hipSuccess;
-    std::vector<float> zero(off, 0.f);
-    ok = ok && hipMemcpy(m->adam_m, zero.data(), sizeof(float) * off, hipMemcpyHostToDevice) ==
-                   hipSuccess;
-    ok = ok && hipMemcpy(m->adam_v, zero.data(), sizeof(float) * off, hipMemcpyHostToDevice) ==
-                   hipSuccess;
-    ok = ok && hipMemcpy(m->grads, zero.data(), sizeof(float) * off, hipMemcpyHostToDevice) ==
-                   hipSuccess;
+    m->params = (float*)(base + at_params);
+    m->grads = (float*)(base + at_grads);
+    m->adam_m = (float*)(base + at_m);
+    m->adam_v = (float*)(base + at_v);
+    m->loss = (float*)(base + at_loss);
+    m->bpack = (float*)(base + at_bpack);
+    m->wpack = (__bf16*)(base + at_wpack);
+    if (m->fused) {
+      m->wtrans = (__bf16*)(base + at_wtrans);
+      m->partial = m->act + act;
+    }
   }
   if (!ok) {
     mgrhd_mlp_destroy(m);
@@ -942,6 +1123,8 @@ int mgrhd_mlp_gradients(mgrhd_mlp* m, const float* X_fm, int64_t ld_x, int64_t r
   if (!m || !X_fm || !Y_target) return MGRHD_E_NULL;
   if (rows < 1 || rows > m->max_rows || ld_x < rows) return MGRHD_E_SIZE;
   hipStream_t s = (hipStream_t)stream;
+  if (m->fused && !m->fp32)
+    return train_pass(m, s, X_fm, ld_x, rows, Y_target, loss_out, false, 0.f);
   forward(m, s, X_fm, ld_x, rows, m->Y, true);
   backward(m, s, X_fm, ld_x, rows, Y_target);
   if (loss_out)
@@ -955,16 +1138,20 @@ int mgrhd_mlp_adam_step(mgrhd_mlp* m, float lr, mgrhd_stream_t stream) {
   hipStream_t s = (hipStream_t)stream;
   m->step += 1;
   m->dirty = true;
-  const float b1 = 0.9f, b2 = 0.999f;
-  const float c1 = 1.f - std::pow(b1, (float)m->step), c2 = 1.f - std::pow(b2, (float)m->step);
+  float b1, b2, eps, c1, c2;
+  adam_factors(m->step, b1, b2, eps, c1, c2);
   hipLaunchKernelGGL(k_adam, grid1(m->n_params), dim3(256), 0, s, m->params, m->grads, m->adam_m,
-                     m->adam_v, m->n_params, lr, b1, b2, 1e-8f, c1, c2);
+                     m->adam_v, m->n_params, lr, b1, b2, eps, c1, c2);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : (int)e;
 }
 
 int mgrhd_mlp_train_step(mgrhd_mlp* m, const float* X_fm, int64_t ld_x, int64_t rows,
                          const float* Y_target, float lr, float* loss_out, mgrhd_stream_t stream) {
+  if (m && X_fm && Y_target && m->fused && !m->fp32) {
+    if (rows < 1 || rows > m->max_rows || ld_x < rows) return MGRHD_E_SIZE;
+    return train_pass(m, (hipStream_t)stream, X_fm, ld_x, rows, Y_target, loss_out, true, lr);
+  }
   int rc = mgrhd_mlp_gradients(m, X_fm, ld_x, rows, Y_target, loss_out, stream);
   if (rc) return rc;
   return mgrhd_mlp_adam_step(m, lr, stream);
@@ -1014,14 +1201,7 @@ static int prepare_infer(mgrhd_mlp* m, hipStream_t s, const float* x_mean, const
                                  96 * 1024) == hipSuccess;
   });
   if (!lds_ok) return MGRHD_E_DEVICE;
-  if (m->dirty) {
-    for (int l = 0; l < 4; ++l)
-      hipLaunchKernelGGL(k_pack, grid1((int64_t)m->n_pad[l] * m->k_pad[l]), dim3(256), 0, s,
-                         m->params + m->w_off[l], m->params + m->b_off[l], m->out_dim[l],
-                         m->in_dim[l], m->n_pad[l], m->k_pad[l], m->wpack + m->wp_off[l],
-                         m->bpack + m->bp_off[l]);
-    m->dirty = false;
-  }
+  pack_weights(m, s);
   std::memset(&q, 0, sizeof(q));
   q.xmean = x_mean;
   q.xistd = x_istd;
@@ -1197,14 +1377,8 @@ int mgrhd_mlp_gemm(const float* A, int32_t lda, int32_t trans_a, const float* B,
 
 void mgrhd_mlp_destroy(mgrhd_mlp* m) {
   if (!m) return;
-  if (m->params) (void)hipFree(m->params);
-  if (m->grads) (void)hipFree(m->grads);
-  if (m->adam_m) (void)hipFree(m->adam_m);
-  if (m->adam_v) (void)hipFree(m->adam_v);
   if (m->act) (void)hipFree(m->act);
-  if (m->loss) (void)hipFree(m->loss);
-  if (m->wpack) (void)hipFree(m->wpack);
-  if (m->bpack) (void)hipFree(m->bpack);
+  if (m->owned) (void)hipFree(m->owned);
   delete m;
 }
 

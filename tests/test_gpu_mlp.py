@@ -289,3 +289,49 @@ def test_inference_against_host_reference():
         print(f"fused={fused}: max rel guess error {e.max():.3e}, median {np.median(e):.3e}")
         assert e.max() < 1e-3, (fused, e.max())
         assert np.median(e) < 1e-5, (fused, np.median(e))
+
+
+# rows off the 32-row tiles and their row ranges, one row, more tiles than
+# workgroups (16384 rows); the narrowest and widest networks of the training
+# kernels, and output widths off 16 and 32
+@pytest.mark.parametrize("ng,rows", [(1, 1), (1, 33), (4, 31), (16, 100), (15, 129), (31, 64),
+                                     (64, 4097), (138, 257), (4, 16417)])
+def test_training_pass_at_tile_edges(ng, rows):
+    """Loss and per-layer gradients of the training kernels against the FP64
+    reference with BF16-rounded operands, at the bounds of
+    test_forward_and_gradients_match_fp64_reference; the step taken with the
+    gradients equals the gradients followed by the Adam step."""
+    rng = np.random.default_rng(ng + rows)
+    net = warmstart.MLP(2 + 3 * ng, 1 + ng, 128, max_rows=rows, seed=ng)
+    p = net.get_params()
+    p[-(3 * 128 + 1 + ng):] = 0.1 * rng.normal(size=3 * 128 + 1 + ng)   # biases
+    net.set_params(p)
+    Ws, bs = net.unpack(p.astype(np.float64))
+    X = rng.normal(size=(rows, net.n_in)).astype(np.float32)
+    T = rng.normal(size=(rows, net.n_out)).astype(np.float32)
+    Xd = torch.from_numpy(np.ascontiguousarray(np.pad(X.T, ((0, 0), (0, 3))))).cuda()
+    Td = torch.from_numpy(T).cuda()
+    loss = float(net.gradients(Xd, Td).cpu())
+    g = net.get_params(which=1)
+    assert np.array_equal(net.get_params(), p)
+    lref, dW, db = mlp_ref.loss_and_grads(Ws, bs, X.astype(np.float64), T.astype(np.float64),
+                                          mlp_ref.bf16_round)
+    assert abs(loss - lref) < 1e-4 * lref
+    gW, gb = net.unpack(g.astype(np.float64))
+    for l in range(4):
+        eW = np.linalg.norm(gW[l] - dW[l]) / np.linalg.norm(dW[l])
+        eb = np.linalg.norm(gb[l] - db[l]) / np.linalg.norm(db[l])
+        assert eW < 1e-3 and eb < 1e-3, (l, eW, eb)
+    L = warmstart._lib()
+    assert L.mgrhd_mlp_adam_step(net._h, 1e-3, net._stream()) == 0
+    other = warmstart.MLP(2 + 3 * ng, 1 + ng, 128, max_rows=rows, seed=ng)
+    other.set_params(p)
+    other.train_step(Xd, Td, 1e-3)
+    assert np.array_equal(other.get_params(which=1), g)
+    a, b = net.get_params(), other.get_params()
+    assert np.abs(a - b).max() <= 2 * np.spacing(np.abs(b).max())
+    # and its BF16 copies are the new weights': the same next gradients
+    net.gradients(Xd, Td)
+    other.set_params(a)
+    other.gradients(Xd, Td)
+    assert np.array_equal(net.get_params(which=1), other.get_params(which=1))
