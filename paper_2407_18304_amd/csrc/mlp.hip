@@ -353,10 +353,15 @@ __global__ void k_guess(PhysArgs p, const float* __restrict__ Yn, const float* _
 // Fused inference: features -> 3 SiLU layers -> output -> Newton guess, one
 // tile of kTile cells per block iteration, activations kept in LDS as BF16.
 // Weights are BF16 copies [N_pad x K_pad] (zero padded) read straight from
-// L2 as matrix-core B fragments; wave w computes n-tiles w, w+4, ... for all
+// L2 as matrix-core B fragments; wave w computes n-tiles w, w+8, ... for all
 // four 16-row tiles, so every weight element is read once per cell tile.
 // Features are formed in FP32 (they are rounded to BF16 for the products).
+// Bound by the feature loads' latency and the features' arithmetic, then by
+// the chain of four products: eight waves with one 16-column tile of a layer
+// each hold a third of the registers of four waves with two, so that three
+// workgroups fit a CU and one's loads run under the others' products.
 constexpr int kTile = 64;
+constexpr int kInferThreads = 512;
 constexpr int kHidden = 128;               // hidden width of the fused path
 constexpr int kHPad = kHidden + 8;         // LDS row pitch of a hidden tile
 constexpr int kMaxKin = 416;               // padded input width (N_g <= 138)
@@ -384,30 +389,20 @@ __device__ __forceinline__ void tile_layer(const __bf16* in, int ldi, const __bf
                                            __bf16* hout, float* fout, int ldo) {
   const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
   const int r16 = lane % 16, kq = 8 * (lane / 16);
-  for (int nt0 = wave; nt0 < n_tiles; nt0 += 8) {
-    // this wave's n-tiles: nt0 and nt0 + 4 (when present)
-    const int nts[2] = {nt0, nt0 + 4};
-    const bool two = nt0 + 4 < n_tiles;
-    floatx4 acc[4][2];
+  for (int nt = wave; nt < n_tiles; nt += kInferThreads / 64) {
+    floatx4 acc[4];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) acc[a][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const __bf16* w0 = W + (int64_t)(16 * nts[0] + r16) * K_pad + kq;
-    const __bf16* w1 = W + (int64_t)(16 * (two ? nts[1] : nts[0]) + r16) * K_pad + kq;
+    for (int a = 0; a < 4; ++a) acc[a] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const __bf16* w0 = W + (int64_t)(16 * nt + r16) * K_pad + kq;
     const int ksteps = K_pad / 32;
     // the B fragments of up to kPre k-steps are requested at once (one L2
     // latency per layer instead of one per k-step)
     constexpr int kPre = 4;
     for (int kb = 0; kb < ksteps; kb += kPre) {
-      bf16x8 bfr[kPre][2];
+      bf16x8 bfr[kPre];
 #pragma unroll
-      for (int kk = 0; kk < kPre; ++kk) {
-        if (kb + kk < ksteps) {
-          bfr[kk][0] = *(const bf16x8*)(w0 + 32 * (kb + kk));
-          bfr[kk][1] = *(const bf16x8*)(w1 + 32 * (kb + kk));
-        }
-      }
+      for (int kk = 0; kk < kPre; ++kk)
+        if (kb + kk < ksteps) bfr[kk] = *(const bf16x8*)(w0 + 32 * (kb + kk));
 #pragma unroll
       for (int kk = 0; kk < kPre; ++kk) {
         if (kb + kk >= ksteps) break;
@@ -415,34 +410,44 @@ __device__ __forceinline__ void tile_layer(const __bf16* in, int ldi, const __bf
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
           const bf16x8 af = *(const bf16x8*)(in + (16 * a + r16) * ldi + k0 + kq);
-          acc[a][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr[kk][0], acc[a][0], 0, 0, 0);
-          if (two)
-            acc[a][1] =
-                __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr[kk][1], acc[a][1], 0, 0, 0);
+          acc[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr[kk], acc[a], 0, 0, 0);
         }
       }
     }
-    const int col16 = lane % 16, row4 = 4 * (lane / 16);
+    const int row4 = 4 * (lane / 16);
+    const int n = 16 * nt + r16;
+    const float bv = bias[n];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      if (t == 1 && !two) break;
-      const int n = 16 * nts[t] + col16;
-      const float bv = bias[n];
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = 16 * a + row4 + i;
-          float z = acc[a][t][i] + bv;
-          if (HIDDEN) {
-            z = z / (1.f + __expf(-z));
-            hout[r * kHPad + n] = (__bf16)z;
-          } else {
-            fout[r * ldo + n] = z;
-          }
+      for (int i = 0; i < 4; ++i) {
+        const int r = 16 * a + row4 + i;
+        float z = acc[a][i] + bv;
+        if (HIDDEN) {
+          z = z / (1.f + __expf(-z));
+          hout[r * kHPad + n] = (__bf16)z;
+        } else {
+          fout[r * ldo + n] = z;
         }
-    }
+      }
   }
+}
+
+// sqrt(a) / b for b > 0 to two roundings: the hardware estimates refined by
+// Newton steps, without the range handling of the general square root and
+// division.  b below 1e-290 counts as that: the caller's a is then 0 (a square
+// below the smallest number), or the quotient past its clamp at 2.
+__device__ __forceinline__ double sqrt_over(double a, double b) {
+  const double y = __builtin_amdgcn_rsq(a);
+  double g = a * y, h = 0.5 * y;
+  const double r = fma(-g, h, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  double d = fma(-g, g, a);
+  g = fma(d, h, g);
+  d = fma(-g, g, a);
+  g = fma(d, h, g);
+  return a > 0.0 ? g * rcp_nr(fmax(b, 1e-290)) : 0.0;
 }
 
 // log of each group's PPL-fixed mean opacity per unit rho kappa (a feature
@@ -455,54 +460,46 @@ __device__ __forceinline__ void infer_lchi(const PhysArgs& p, float* lchi) {
   }
 }
 
+// What the threads of a cell share while its tile is inferred.
+struct CellScalars {
+  double Tc[kTile], rh[kTile], ke[kTile], iaT4[kTile];
+  float lcell[kTile];
+};
+
 // The fused inference of the cells [i0, min(i0 + kTile, i1)) of one state:
 // features, the three hidden layers and the output on the matrix cores, and
 // the Newton guess written to `guess` (kind 1: [n]; kind 0: [N_g+1][n]).
 // Every thread of the workgroup calls it (it synchronises); smem is the
 // dynamic LDS of k_infer, lchi that state's feature table.
 __device__ __forceinline__ void infer_tile(const InferArgs& q, const PhysArgs& p, double* guess,
-                                           const double* S, const float* lchi, const float* xs,
+                                           const double* S, const float* lchi, float* xs,
                                            int64_t i0, int64_t i1, unsigned char* smem) {
   const int ng = p.ng;
   const int64_t n = p.n;
   const int ldx = q.K_pad[0] + 8;
   __bf16* X = (__bf16*)smem;                                  // [kTile][ldx]; later H_b / out
   __bf16* Ha = X + kTile * (ldx > kHPad ? ldx : kHPad);       // [kTile][kHPad]
-  const int r = threadIdx.x / 4, qd = threadIdx.x % 4;
+  // eight threads per cell: a wave loads 16 cells of four groups, whole lines
+  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  constexpr int kQ = kInferThreads / kTile;
+  const int r = 16 * (wave % 4) + lane % 16, qd = 4 * (wave / 4) + lane / 16;
   const int64_t i = i0 + r;
   const bool live = i < i1;
-  // the cell's temperature, density and kinetic energy, kept for the guess
-  double Tc = 1.0, rh = 1.0, ke = 0.0;
+  // the cells' temperatures, densities and kinetic energies, kept for the guess
+  CellScalars& cs = *(CellScalars*)(xs + 2 * q.K_pad[0]);
   // ---- features (normalised, bf16) ----
   {
-    float T = 1.f, rho = 1.f, lcell = 0.f;
-    double iaT4 = 1.0;  // 1/(a T^4)
-    if (live) {
-      const double v0 = p.v[i], v1 = p.v[n + i], v2 = p.v[2 * n + i];
-      rh = p.rho[i];
-      ke = 0.5 * rh * (v0 * v0 + v1 * v1 + v2 * v2);
-      Tc = fmax((p.egas[i] - ke) / (rh * p.cv), 1e-300);
-      const double kap = p.kappa ? p.kappa[i] : 1.0;
-      T = (float)Tc;
-      rho = (float)rh;
-      iaT4 = 1.0 / (p.a * (Tc * Tc) * (Tc * Tc));
-      lcell = (float)log(p.chat * p.dt * rh * kap);
-    }
     __bf16* xr = X + r * ldx;
     // xs: the input statistics in LDS, mean [K_pad] then 1/std [K_pad]
     auto put = [&](int f, float x) { xr[f] = (__bf16)((x - xs[f]) * xs[q.K_pad[0] + f]); };
-    if (qd == 0) {
-      put(0, live ? __logf(T) : 0.f);
-      put(1, live ? __logf(rho) : 0.f);
-    }
-    // sixteen groups per chunk: their 64 loads are in flight together (all of
-    // a thread's loads at 64 groups)
-    constexpr int kU = 16;
-    for (int g0 = qd; g0 < ng; g0 += 4 * kU) {
-      double E[kU], f0[kU], f1[kU], f2[kU];
+    // four groups per chunk, their 16 loads in flight together, the first under
+    // the cells' scalars
+    constexpr int kU = 4;
+    double E[kU], f0[kU], f1[kU], f2[kU];
+    auto load = [&](int g0) {
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
-        const int g = g0 + 4 * u;
+        const int g = g0 + kQ * u;
         E[u] = f0[u] = f1[u] = f2[u] = 0.0;
         if (live && g < ng) {
           E[u] = p.E[(int64_t)g * n + i];
@@ -511,24 +508,53 @@ __device__ __forceinline__ void infer_tile(const InferArgs& q, const PhysArgs& p
           f2[u] = p.F[((int64_t)2 * ng + g) * n + i];
         }
       }
+    };
+    load(qd);
+    if (qd == 0) {
+      double Tc = 1.0, rh = 1.0, ke = 0.0, iaT4 = 1.0;  // iaT4 = 1/(a T^4)
+      float T = 1.f, rho = 1.f, lcell = 0.f;
+      if (live) {
+        const double v0 = p.v[i], v1 = p.v[n + i], v2 = p.v[2 * n + i];
+        rh = p.rho[i];
+        ke = 0.5 * rh * (v0 * v0 + v1 * v1 + v2 * v2);
+        Tc = fmax((p.egas[i] - ke) / (rh * p.cv), 1e-300);
+        const double kap = p.kappa ? p.kappa[i] : 1.0;
+        T = (float)Tc;
+        rho = (float)rh;
+        iaT4 = 1.0 / (p.a * (Tc * Tc) * (Tc * Tc));
+        lcell = (float)log(p.chat * p.dt * rh * kap);
+      }
+      cs.Tc[r] = Tc;
+      cs.rh[r] = rh;
+      cs.ke[r] = ke;
+      cs.iaT4[r] = iaT4;
+      cs.lcell[r] = lcell;
+      put(0, live ? __logf(T) : 0.f);
+      put(1, live ? __logf(rho) : 0.f);
+    }
+    __syncthreads();
+    const double iaT4 = cs.iaT4[r];
+    const float lcell = cs.lcell[r];
+    for (int g0 = qd; g0 < ng; g0 += kQ * kU) {
+      if (g0 != qd) load(g0);
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
-        const int g = g0 + 4 * u;
+        const int g = g0 + kQ * u;
         if (g >= ng) break;
         float le = -50.f, fr = 0.f;
         if (E[u] > 0.0) {
           // E / (a T^4) rounded to FP32: beyond its range the logarithm is
           // past the clamp at +-50 either way
           le = fminf(fmaxf(__logf((float)(E[u] * iaT4)), -50.f), 50.f);
-          fr = fminf((float)(sqrt(f0[u] * f0[u] + f1[u] * f1[u] + f2[u] * f2[u]) /
-                             (p.c * E[u])), 2.f);
+          fr = fminf((float)sqrt_over(f0[u] * f0[u] + f1[u] * f1[u] + f2[u] * f2[u],
+                                      p.c * E[u]), 2.f);
         }
         put(2 + g, le);
         put(2 + ng + g, fr);
         put(2 + 2 * ng + g, lcell + lchi[g]);
       }
     }
-    for (int f = q.n_in + qd; f < q.K_pad[0]; f += 4) xr[f] = (__bf16)0.f;
+    for (int f = q.n_in + qd; f < q.K_pad[0]; f += kQ) xr[f] = (__bf16)0.f;
   }
   __syncthreads();
   // ---- layers: X -> Ha -> Hb (in X's space) -> Ha -> out (fp32 in X's space) ----
@@ -547,13 +573,14 @@ __device__ __forceinline__ void infer_tile(const InferArgs& q, const PhysArgs& p
   // ---- Newton guess ----
   if (live) {
     const float* o = out + r * ldo;
+    const double Tc = cs.Tc[r];
     if (qd == 0) {
       const double yT = (double)o[0] * q.ystd[0] + q.ymean[0];
-      guess[i] = rh * p.cv * Tc * exp(fmin(fmax(yT, -5.0), 5.0)) + ke;
+      guess[i] = cs.rh[r] * p.cv * Tc * exp(fmin(fmax(yT, -5.0), 5.0)) + cs.ke[r];
     }
     if (q.kind == 0) {
       const double aT4 = p.a * (Tc * Tc) * (Tc * Tc);
-      for (int g = qd; g < ng; g += 4) {
+      for (int g = qd; g < ng; g += kQ) {
         const double yE = (double)o[1 + g] * q.ystd[1 + g] + q.ymean[1 + g];
         const double sg = S ? S[(int64_t)g * n + i] : 0.0;
         guess[(int64_t)(g + 1) * n + i] =
@@ -565,13 +592,13 @@ __device__ __forceinline__ void infer_tile(const InferArgs& q, const PhysArgs& p
 }
 
 // LDS of the fused inference: the input tile (or a hidden tile), a hidden
-// tile, the feature table of N_g floats and the input statistics (2 K_pad
-// floats, after the table at a K_pad-float offset: N_g <= K_pad).
+// tile, the feature table of N_g floats, the input statistics (2 K_pad floats,
+// after the table at a K_pad-float offset: N_g <= K_pad) and the cells' scalars.
 __host__ __device__ inline size_t infer_lds_bytes(int k_pad0, int ng) {
   const int ldx = k_pad0 + 8;
   (void)ng;
   return sizeof(__bf16) * (size_t)kTile * ((ldx > kHPad ? ldx : kHPad) + kHPad) +
-         sizeof(float) * 3 * (size_t)k_pad0;
+         sizeof(float) * 3 * (size_t)k_pad0 + sizeof(CellScalars);
 }
 
 // The input statistics into LDS (mean, then 1/std; zero beyond n_in).
@@ -582,7 +609,20 @@ __device__ __forceinline__ void infer_stats(const InferArgs& q, float* xs) {
   }
 }
 
-__global__ __launch_bounds__(256, 2) void k_infer(InferArgs q) {
+// The launch's arguments as they stand in the kernel-argument segment, read
+// anew for every tile (their address passes through an empty asm): hoisted out
+// of the loop over tiles, the weights of all layers and the rows' addresses
+// held 160 registers too many, in scratch.
+typedef const InferArgs __attribute__((address_space(4)))* InferArgsRef;
+__device__ __forceinline__ InferArgs infer_args() {
+  InferArgsRef qp = (InferArgsRef)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(qp));
+  InferArgs q;
+  __builtin_memcpy(&q, (const InferArgs*)qp, sizeof(InferArgs));
+  return q;
+}
+
+__global__ __launch_bounds__(kInferThreads, 4) void k_infer(InferArgs q) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const PhysArgs& p = q.p;
   const int ldx = q.K_pad[0] + 8;
@@ -593,8 +633,10 @@ __global__ __launch_bounds__(256, 2) void k_infer(InferArgs q) {
   infer_stats(q, xs);
   __syncthreads();
   const int64_t tiles = (p.n + kTile - 1) / kTile;
-  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x)
-    infer_tile(q, p, q.guess, q.S, lchi, xs, tile * kTile, p.n, smem);
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const InferArgs t = infer_args();
+    infer_tile(t, t.p, t.guess, t.S, lchi, xs, tile * kTile, t.p.n, smem);
+  }
 }
 
 // The fused inference over the work items [lo, hi) of a batch of patches
@@ -602,13 +644,46 @@ __global__ __launch_bounds__(256, 2) void k_infer(InferArgs q) {
 // feature table when the patch changes, and infers the item's cells tile by
 // tile into that patch's guess buffer.
 struct InferItemsArgs {
-  InferArgs q;          // weights, statistics, kind (q.p, q.guess, q.S unused)
+  InferArgs q;          // first (infer_args): weights, statistics, kind (q.p, q.guess, q.S unused)
   const KArgs* patches;
   const BatchItem* items;
   int64_t lo, hi;
 };
 
-__global__ __launch_bounds__(256, 2) void k_infer_items(InferItemsArgs a) {
+// A patch's state, guess buffer and source, read anew for every tile as
+// infer_args.
+struct PatchArgs {
+  PhysArgs p;
+  double* guess;
+  const double* S;
+};
+__device__ __forceinline__ PatchArgs patch_args(const KArgs* patch) {
+  KArgsRef k = (KArgsRef)patch;
+  asm volatile("" : "+s"(k));
+  PatchArgs r;
+  r.p.E = k->E;
+  r.p.F = k->F;
+  r.p.rho = k->rho;
+  r.p.egas = k->egas;
+  r.p.v = k->v;
+  r.p.kappa = k->kappa;
+  r.p.edges = k->edges;
+  r.p.chi_lo = k->chi_lo;
+  r.p.alpha = k->alpha;
+  r.p.n = k->n;
+  r.p.ng = k->ng;
+  r.p.pad = 0;
+  r.p.dt = k->dt;
+  r.p.chat = k->chat;
+  r.p.c = k->c;
+  r.p.a = k->a;
+  r.p.cv = k->cv;
+  r.guess = const_cast<double*>(k->guess);  // the batch's guess buffer
+  r.S = k->S;
+  return r;
+}
+
+__global__ __launch_bounds__(kInferThreads, 4) void k_infer_items(InferItemsArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int ldx = a.q.K_pad[0] + 8;
   float* lchi = (float*)(smem + sizeof(__bf16) * (size_t)kTile *
@@ -616,36 +691,21 @@ __global__ __launch_bounds__(256, 2) void k_infer_items(InferItemsArgs a) {
   float* xs = lchi + a.q.K_pad[0];
   infer_stats(a.q, xs);  // (published by the first patch's barrier below)
   int cur = -1;
+  typedef const BatchItem __attribute__((address_space(4)))* ItemRef;
   for (int64_t it = a.lo + blockIdx.x; it < a.hi; it += gridDim.x) {
-    const BatchItem item = a.items[it];
-    const KArgs& k = a.patches[item.patch];
-    PhysArgs p;
-    p.E = k.E;
-    p.F = k.F;
-    p.rho = k.rho;
-    p.egas = k.egas;
-    p.v = k.v;
-    p.kappa = k.kappa;
-    p.edges = k.edges;
-    p.chi_lo = k.chi_lo;
-    p.alpha = k.alpha;
-    p.n = k.n;
-    p.ng = k.ng;
-    p.pad = 0;
-    p.dt = k.dt;
-    p.chat = k.chat;
-    p.c = k.c;
-    p.a = k.a;
-    p.cv = k.cv;
-    if (item.patch != cur) {  // uniform over the workgroup
-      __syncthreads();        // the previous patch's table is no longer read
-      infer_lchi(p, lchi);
+    const ItemRef item = (ItemRef)(a.items + it);
+    const int patch = item->patch;
+    const int64_t c0 = item->c0, c1 = item->c1;
+    if (patch != cur) {  // uniform over the workgroup
+      __syncthreads();   // the previous patch's table is no longer read
+      infer_lchi(patch_args(a.patches + patch).p, lchi);
       __syncthreads();
-      cur = item.patch;
+      cur = patch;
     }
-    double* guess = const_cast<double*>(k.guess);  // the batch's guess buffer
-    for (int64_t i0 = item.c0; i0 < item.c1; i0 += kTile)
-      infer_tile(a.q, p, guess, k.S, lchi, xs, i0, item.c1, smem);
+    for (int64_t i0 = c0; i0 < c1; i0 += kTile) {
+      const PatchArgs k = patch_args(a.patches + patch);
+      infer_tile(infer_args(), k.p, k.guess, k.S, lchi, xs, i0, c1, smem);
+    }
   }
 }
 
@@ -1256,7 +1316,7 @@ int mlp_infer_items(mgrhd_mlp* m, const KArgs* d_patches, const BatchItem* d_ite
   a.hi = hi;
   const int64_t cap = (int64_t)num_cus() * 4;
   const int64_t blocks = (hi - lo) < cap ? (hi - lo) : cap;
-  hipLaunchKernelGGL(k_infer_items, dim3((unsigned)blocks), dim3(256),
+  hipLaunchKernelGGL(k_infer_items, dim3((unsigned)blocks), dim3(kInferThreads),
                      infer_lds_bytes(m->k_pad[0], n_groups), s, a);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : (int)e;
@@ -1339,7 +1399,7 @@ int mgrhd_mlp_infer(mgrhd_mlp* m, const double* E_g, const double* F_g, const do
   const int64_t tiles = (n + kTile - 1) / kTile;
   const int64_t cap = (int64_t)num_cus() * 4;
   const int64_t blocks = tiles < cap ? tiles : cap;
-  hipLaunchKernelGGL(k_infer, dim3((unsigned)blocks), dim3(256),
+  hipLaunchKernelGGL(k_infer, dim3((unsigned)blocks), dim3(kInferThreads),
                      infer_lds_bytes(m->k_pad[0], p.ng), s, q);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : (int)e;
