@@ -8,9 +8,10 @@
 // Per edge x:
 //   x <= 4  cumulative fraction P(x) = (15/pi^4) x^3 (1/3 - x/8 + y Ap(y)),
 //           y = x^2, Ap a near-minimax polynomial (planck_poly.inc);
-//   x >  4  e^x Q(x) = (15/pi^4) sum_{k=1..10} e^{-(k-1)x} (x^3/k + 3x^2/k^2
-//           + 6x/k^3 + 6/k^4), the geometric series of 1/(e^t - 1), whose
-//           11th term is below 2e-18 of the first for x > 4;
+//   x >  4  e^x Q(x) = (15/pi^4) sum_k e^{-(k-1)x} (x^3/k + 3x^2/k^2
+//           + 6x/k^3 + 6/k^4), the geometric series of 1/(e^t - 1), each of
+//           the four sums to the term that is below 1.1e-17 of the whole for
+//           x > 4 (kTailTerms);
 //   x <= 4  x/(e^x - 1) = 1 - x/2 + y Ep(y) (no exponential: an edge below the
 //           Wien side costs two polynomials, the same instructions in every lane);
 //   x >  4  x/(e^x - 1) from u = e^{-x}.
@@ -25,7 +26,10 @@ namespace mgrhd {
 
 constexpr double kPi = 3.14159265358979323846264338327950288;
 constexpr double kC15 = 15.0 / (kPi * kPi * kPi * kPi);
-constexpr int kTailTerms = 10;
+// terms of S_1 .. S_4 of the Wien tail: what is left out adds up to 2.1e-17 of
+// e^x Q at x = 4 (1.0e-17 + 0.8e-18 + 2.9e-18 + 7.1e-18), a fifth of the
+// rounding of the result, and falls as e^{-9x}, e^{-8x}, e^{-7x}
+constexpr int kTailTerms[4] = {9, 9, 8, 7};
 
 // 1/k^j, the coefficient of u^{k-1} in S_j(u) of the Wien tail
 __host__ __device__ constexpr double tail_coef(int k, int j) {
@@ -49,8 +53,8 @@ __host__ __device__ __forceinline__ double fma_c(double a, double b, double c) {
 #endif
 }
 
-// 1/d for |d| in [2^-1000, 2^1000] (the callers' denominators are bounded
-// away from 0 and overflow): the hardware estimate refined by two
+// 1/d for |d| in [2^-1021, 2^1021] (the callers' denominators are bounded
+// away from 0 and overflow, or tested after): the hardware estimate refined by two
 // Newton-Raphson steps, within an ulp, without the scaling and fix-up steps
 // of a general division.  The host build divides.
 __host__ __device__ __forceinline__ double rcp_nr(double d) {
@@ -62,6 +66,18 @@ __host__ __device__ __forceinline__ double rcp_nr(double d) {
   return fma(e, r, r);
 #else
   return 1.0 / d;
+#endif
+}
+
+// n/d for d in the range of rcp_nr: the quotient's residual corrects it to the
+// last place, so it is the general division's but for a rare rounding.
+__host__ __device__ __forceinline__ double div_nr(double n, double d) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double r = rcp_nr(d);
+  const double q = n * r;
+  return fma(fma(-d, q, n), r, q);
+#else
+  return n / d;
 #endif
 }
 
@@ -110,6 +126,51 @@ __host__ __device__ __forceinline__ double exp_neg(double x) {
   return ldexp(p, -static_cast<int>(fmax(n, 0.0)));   // a NaN n converts as 0
 }
 
+// 1 - e^{-t} and e^{-t} for t >= 0, both to a few roundings whatever t: the
+// reduction and the series of exp_neg, without the series' leading 1, so that
+// nothing cancels near 0: with s = 2^{-n} and e^{-r} = 1 + p,
+// 1 - e^{-t} = (1 - s) - s p.  23 instructions against the 34 of expm1 and 29
+// of exp that it stands for in the group means.
+struct OneMinusExp {
+  double em, e;
+};
+__host__ __device__ __forceinline__ OneMinusExp one_minus_exp(double t) {
+  const double tc = t > 746.0 ? 746.0 : t;
+  const double n = rint(tc * kInvLn2);
+  const double mr = fma(n, kLn2Lo, fma(n, kLn2Hi, -tc));   // -r
+  double p = inv_factorial(kExpDeg);
+#pragma unroll
+  for (int k = kExpDeg - 1; k >= 1; --k) p = fma_c(p, mr, inv_factorial(k));
+  p *= mr;
+  const double s = ldexp(1.0, -static_cast<int>(fmax(n, 0.0)));   // a NaN n converts as 0
+  return {fma(-s, p, 1.0 - s), fma(s, p, s)};
+}
+
+// ln x for finite x > 0 (subnormals included), within 2 ulp: x = 2^e m with
+// m in [sqrt(1/2), sqrt(2)), ln m = 2 atanh(s) with s = (m - 1)/(m + 1) by its
+// Taylor series to s^21 (|s| < 0.1716: remainder below 1e-18 relative).
+constexpr int kLogTerms = 10;
+__host__ __device__ __forceinline__ double log_pos(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  double m = __builtin_amdgcn_frexp_mant(x);
+  int e = __builtin_amdgcn_frexp_exp(x);
+#else
+  int e = 0;
+  double m = frexp(x, &e);
+#endif
+  const bool low = m < 0.70710678118654752440;
+  m = low ? 2.0 * m : m;
+  e = low ? e - 1 : e;
+  const double f = m - 1.0;
+  const double s = f * rcp_nr(2.0 + f);
+  const double z = s * s;
+  double q = 2.0 / (2 * kLogTerms + 1);
+#pragma unroll
+  for (int k = kLogTerms - 1; k >= 1; --k) q = fma_c(q, z, 2.0 / (2 * k + 1));
+  const double ed = static_cast<double>(e);
+  return fma(ed, kLn2Hi, fma(s, z * q, fma(ed, kLn2Lo, s + s)));
+}
+
 // +inf test usable on host and device
 __host__ __device__ __forceinline__ bool is_pinf(double x) { return x > 1.7976931348623157e308; }
 
@@ -128,7 +189,7 @@ struct Edge {
 // the Wien side x/(x + x/(e^x - 1)), with no exponential; beyond it 1 - u.
 // Needs x > 0 below the Wien side.
 __host__ __device__ __forceinline__ double stim_factor(const Edge& e) {
-  return e.wien ? 1.0 - e.u : e.x / (e.x + e.eb);
+  return e.wien ? 1.0 - e.u : e.x * rcp_nr(e.x + e.eb);   // x + x/(e^x - 1) in [1, 5]
 }
 
 __host__ __device__ __forceinline__ Edge planck_edge(double x) {
@@ -161,14 +222,14 @@ __host__ __device__ __forceinline__ Edge planck_edge(double x) {
     // sum_k u^{k-1} (x^3/k + 3x^2/k^2 + 6x/k^3 + 6/k^4) as
     // x^3 S1(u) + 3x^2 S2(u) + 6x S3(u) + 6 S4(u), S_j(u) = sum_k u^{k-1}/k^j:
     // four Horner chains in u with constant coefficients 1/k^j
-    double s1 = tail_coef(kTailTerms, 1), s2 = tail_coef(kTailTerms, 2);
-    double s3 = tail_coef(kTailTerms, 3), s4 = tail_coef(kTailTerms, 4);
+    double s1 = tail_coef(kTailTerms[0], 1), s2 = tail_coef(kTailTerms[1], 2);
+    double s3 = tail_coef(kTailTerms[2], 3), s4 = tail_coef(kTailTerms[3], 4);
 #pragma unroll
-    for (int k = kTailTerms - 1; k >= 1; --k) {
+    for (int k = kTailTerms[0] - 1; k >= 1; --k) {
       s1 = fma_c(s1, u, tail_coef(k, 1));
-      s2 = fma_c(s2, u, tail_coef(k, 2));
-      s3 = fma_c(s3, u, tail_coef(k, 3));
-      s4 = fma_c(s4, u, tail_coef(k, 4));
+      if (k < kTailTerms[1]) s2 = fma_c(s2, u, tail_coef(k, 2));
+      if (k < kTailTerms[2]) s3 = fma_c(s3, u, tail_coef(k, 3));
+      if (k < kTailTerms[3]) s4 = fma_c(s4, u, tail_coef(k, 4));
     }
     e.val = kC15 * fma(x3, s1, fma(3.0 * y, s2, fma(6.0 * x, s3, 6.0 * s4)));
     e.eps = kC15 * x3 * x * rcp_nr(1.0 - u);   // 1 - u in [0.98, 1)
@@ -223,7 +284,7 @@ __host__ __device__ __forceinline__ GroupPlanck group_planck(const Edge& lo, con
     if (hi.inf)
       d = 0.0;
     else if (lo.x < 700.0)
-      d = hi.u / lo.u;
+      d = div_nr(hi.u, lo.u);
     else
       d = exp_neg(hi.x - lo.x);
     p.b = lo.val - d * hi.val;
@@ -269,6 +330,31 @@ __host__ __device__ __forceinline__ double mean_ratio(double ac, double aq, doub
   const double den = phi_scaled(aq + 1.0, L, m2);
   const double r = num / den;
   return (m1 == m2) ? r : r * exp(m1 - m2);
+}
+
+// mean_ratio for the kernels' inner loop, given rac = e^{ac L}: with t = |a L|
+// the bracket of eq. chiQg is (1 - e^{-t})/t times e^{max(aL, 0)}, and the
+// ratio of the two scale factors follows from rac and e^{-t2}, so a mean takes
+// two exponentials and one reciprocal (two expm1, an exp and three divisions
+// in mean_ratio).
+__host__ __device__ __forceinline__ double mean_ratio_rac(double ac, double aq, double L,
+                                                          double rac) {
+  const double y1 = (ac + aq + 1.0) * L, y2 = (aq + 1.0) * L;
+  const double t1 = fabs(y1), t2 = fabs(y2);
+  const OneMinusExp o1 = one_minus_exp(t1), o2 = one_minus_exp(t2);
+  const double n1 = y1 == 0.0 ? 1.0 : o1.em, d1 = y1 == 0.0 ? 1.0 : t1;
+  const double n2 = y2 == 0.0 ? 1.0 : o2.em, d2 = y2 == 0.0 ? 1.0 : t2;
+  const double r = (n1 * d2) * rcp_nr(n2 * d1);
+  const double up = y2 > 0.0 ? 1.0 : o2.e;           // e^{y1} = e^{y2} rac
+  return r * (y1 > 0.0 ? up * rac : (y2 > 0.0 ? o2.e : 1.0));
+}
+
+// The same at alpha_Q = -1: (e^y - 1)/y with y = ac L and rac = e^y.
+__host__ __device__ __forceinline__ double mean_fixed_rac(double y, double rac) {
+  const double t = fabs(y);
+  const OneMinusExp o = one_minus_exp(t);
+  const double r = y == 0.0 ? 1.0 : o.em * rcp_nr(t);
+  return y > 0.0 ? r * rac : r;
 }
 
 __host__ __device__ __forceinline__ double minmod(double a, double b) {

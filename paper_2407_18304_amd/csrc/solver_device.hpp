@@ -185,7 +185,7 @@ struct Tables {
   double chk[NGM];    // PC / PPL-fixed group mean per unit rho * kappa (chit, or chit * mfix)
   double rac[NGM];    // r_g^alpha_chi
   double lndnu[NGM];  // ln(nu_g+ - nu_g-)
-  double lnc[NGM];    // (ln nu_g- + ln nu_g+)/2
+  double rdl[NGM];    // 1 / (distance of ln nu at the centres of groups g - 1 and g); g > 0
   int bad;
 };
 
@@ -293,7 +293,7 @@ __device__ __forceinline__ bool table_group(const KArgs& a, Tables<NGM>& t, int 
   const double lo = t.nu[g], hi = t.nu[g + 1];
   const double chl = a.chi_lo[g];
   bool ok = hi > lo && chl > 0.0 && !is_pinf(chl);
-  double L = 0.0, ac = 0.0, mf = 1.0, rac = 1.0, ldn = 0.0, lc = 0.0;
+  double L = 0.0, ac = 0.0, mf = 1.0, rac = 1.0, ldn = 0.0, rdl = 0.0;
   if (MODE != MGRHD_MEAN_PC) {
     L = log(hi / lo);
     if (a.alpha) {
@@ -307,7 +307,8 @@ __device__ __forceinline__ bool table_group(const KArgs& a, Tables<NGM>& t, int 
     mf = mean_ratio(ac, -1.0, L);
     rac = exp(ac * L);
     ldn = log(hi - lo);
-    lc = 0.5 * (log(lo) + log(hi));
+    if (MODE == MGRHD_MEAN_PPL_FREE && g > 0)
+      rdl = 1.0 / (0.5 * (log(lo) + log(hi)) - 0.5 * (log(t.nu[g - 1]) + log(lo)));
   }
   t.lnr[g] = L;
   t.achi[g] = ac;
@@ -316,7 +317,7 @@ __device__ __forceinline__ bool table_group(const KArgs& a, Tables<NGM>& t, int 
   t.chk[g] = (MODE == MGRHD_MEAN_PC) ? chl : chl * mf;
   t.rac[g] = rac;
   t.lndnu[g] = ldn;
-  t.lnc[g] = lc;
+  t.rdl[g] = rdl;
   return ok;
 }
 
@@ -421,8 +422,8 @@ __device__ __forceinline__ void slopes_free(const Tables<NGM>& t, int ng, int j,
     const int g = gidx<LPC>(j, k, lpc);
     alpha[k] = -1.0;
     if (g <= 0 || g >= ng - 1) continue;
-    const double sl = (lq[k] - lm) / (t.lnc[g] - t.lnc[g - 1]);
-    const double sr = (lp - lq[k]) / (t.lnc[g + 1] - t.lnc[g]);
+    const double sl = (lq[k] - lm) * t.rdl[g];
+    const double sr = (lp - lq[k]) * t.rdl[g + 1];
     if (isnan(sl) || isnan(sr)) continue;
     const double m = minmod(sl, sr);
     if (isfinite(m)) alpha[k] = m;
@@ -506,7 +507,7 @@ __device__ __forceinline__ void evaluate(const Tables<NGM>& t, int ng, int j, in
           // eq. chiDiff with numerator and denominator both multiplied by 3
           const double num = (4.0 + ac) * ch * p.b - dchib;
           const double den = 4.0 * p.b - (p.ehi - p.elo);
-          const double f = num / den;
+          const double f = div_nr(num, den);
           c.chiF[k] = (den > 0.0 && isfinite(f)) ? f : ch;
           c.emit[k] = ch * Bt - aT4 * dchib * p.scale * kThird;
         }
@@ -520,16 +521,17 @@ __device__ __forceinline__ void evaluate(const Tables<NGM>& t, int ng, int j, in
         } else {
           double ac = t.achi[g], rac = t.rac[g], mr = t.mfix[g];
           if (ot.stim) {
-            const double q = s_hi / s_lo;
-            ac += log(q) / t.lnr[g];
+            const double q = s_hi * rcp_nr(s_lo);
+            const double lq = log_pos(q);
+            mr = mean_fixed_rac(fma(ac, t.lnr[g], lq), rac * q);  // eq. chiQg, alpha_Q = -1
+            ac = fma(lq, rcp_nr(t.lnr[g]), ac);
             rac *= q;
-            mr = mean_ratio(ac, -1.0, t.lnr[g]);  // eq. chiQg, alpha_Q = -1
           }
           const double ch = chl * mr;
           const double dchib = chl * (rac * p.ehi - p.elo);
           const double num = (4.0 + ac) * ch * p.b - dchib;
           const double den = 4.0 * p.b - (p.ehi - p.elo);
-          const double f = num / den;
+          const double f = div_nr(num, den);
           c.chiE[k] = ch;
           c.ac[k] = ac;
           c.chiF[k] = (den > 0.0 && isfinite(f)) ? f : ch;
@@ -551,7 +553,7 @@ __device__ __forceinline__ void evaluate(const Tables<NGM>& t, int ng, int j, in
         const double s_hi = stim_factor(hi);
         slo[k] = from_left<LPC>(last ? prev_s : s_hi, lpc);
         prev_s = s_hi;
-        sq[k] = s_hi / slo[k];
+        sq[k] = s_hi * rcp_nr(slo[k]);
       }
       lqB[k] = -INFINITY;
       lqE[k] = -INFINITY;
@@ -564,8 +566,8 @@ __device__ __forceinline__ void evaluate(const Tables<NGM>& t, int ng, int j, in
       ehi[k] = p.ehi;
       sig[k] = p.sigma;
       scale[k] = p.scale;
-      if (p.b > 0.0) lqB[k] = log(p.b) - p.sigma - t.lndnu[g];
-      if (Ecur[k] > 0.0) lqE[k] = log(Ecur[k]) - t.lndnu[g];
+      if (p.b > 0.0) lqB[k] = log_pos(p.b) - p.sigma - t.lndnu[g];
+      if (Ecur[k] > 0.0) lqE[k] = log_pos(Ecur[k]) - t.lndnu[g];
     }
     slopes_free<G, LPC, NGM>(t, ng, j, lpc, lqB, aB);
     slopes_free<G, LPC, NGM>(t, ng, j, lpc, lqE, aE);
@@ -578,7 +580,7 @@ __device__ __forceinline__ void evaluate(const Tables<NGM>& t, int ng, int j, in
       if (TD) {
         chl *= ot.fT * slo[k];
         if (ot.stim) {
-          ac += log(sq[k]) / L;
+          ac = fma(log_pos(sq[k]), rcp_nr(L), ac);
           rac *= sq[k];
         }
         c.ac[k] = ac;
@@ -587,14 +589,14 @@ __device__ __forceinline__ void evaluate(const Tables<NGM>& t, int ng, int j, in
       const double Dnu = aT4 * (ehi[k] - elo[k]) * scale[k];
       c.Bt[k] = Bt;
       c.dBdT[k] = (4.0 * Bt - Dnu) * invT;
-      const double chB = chl * mean_ratio(ac, aB[k], L);
-      const double chE = chl * mean_ratio(ac, aE[k], L);
+      const double chB = chl * mean_ratio_rac(ac, aB[k], L, rac);
+      const double chE = chl * mean_ratio_rac(ac, aE[k], L, rac);
       c.chiB[k] = chB;
       c.chiE[k] = chE;
       const double dchib = chl * (rac * ehi[k] - elo[k]);
       const double num = (3.0 * chB + (1.0 + ac) * chE) * b[k] - dchib;  // both times 3
       const double den = 4.0 * b[k] - (ehi[k] - elo[k]);
-      const double f = num / den;
+      const double f = div_nr(num, den);
       c.chiF[k] = (den > 0.0 && isfinite(f)) ? f : chE;
       c.emit[k] = chB * Bt - aT4 * dchib * scale[k] * kThird;
     }
@@ -891,8 +893,8 @@ __device__ __forceinline__ void newton_step(const KArgs& a, const Tables<NGM>& t
     if (g >= ng) continue;
     double ratio = 1.0, itau, iJgg;
     if (MODE == MGRHD_MEAN_PPL_FREE || TD) {
-      if (MODE == MGRHD_MEAN_PPL_FREE) ratio = c.chiB[k] / c.chiE[k];
-      itau = 1.0 / (cdt * c.chiE[k]);
+      if (MODE == MGRHD_MEAN_PPL_FREE) ratio = div_nr(c.chiB[k], c.chiE[k]);
+      itau = rcp_nr(cdt * c.chiE[k]);
       iJgg = rcp_nr(-itau - 1.0);  // |-itau - 1| >= 1
     } else {
       itau = ls.itau(k);
@@ -1122,7 +1124,7 @@ __device__ __forceinline__ void run_cells(const KArgs& a, const Tables<NGM>& tab
     OpacityT ot{1.0, false};
     if (TD) {
       const double t_exp = ls.cst(a, &KArgs::t_exp);
-      ot.fT = t_exp != 0.0 ? exp(t_exp * log(T * ls.cst(a, &KArgs::itref))) : 1.0;
+      ot.fT = t_exp != 0.0 ? exp(t_exp * log_pos(T * ls.cst(a, &KArgs::itref))) : 1.0;
       ot.stim = ls.cst(a, &KArgs::stim) != 0;
     }
     evaluate<G, LPC, MODE, NGM, TD>(tab, group_count<G, LPC, FULL>(a), j, s.lpc, T, aT4,
