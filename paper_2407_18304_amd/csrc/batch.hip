@@ -219,12 +219,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_wg(BatchArgs b) {
 template <int G, int LPC, int MODE, bool FULL>
 __device__ __forceinline__ void run_item_block(const KArgs& a, KArgsRef ap, const Item& item,
                                                unsigned char* lds) {
-  run_block<G, LPC, MODE, false, FULL>(a, ap, item.c0, item.c1, *(BlockLds<G, LPC, true>*)lds);
+  run_block<G, LPC, MODE, false, FULL>(a, ap, item.c0, item.c1, *(BlockLds<G, LPC, FULL, true>*)lds);
 }
 
 template <int G, int MODE, bool FULL>
-__global__ __launch_bounds__(kBlock, FULL ? 4 : 3) void k_batch_items(const KArgs* patches,
-                                                                      const Item* items) {
+__global__ __launch_bounds__((block_threads<G, FULL>()), FULL ? 4 : 3) void k_batch_items(
+    const KArgs* patches, const Item* items) {
   extern __shared__ __attribute__((aligned(16))) unsigned char batch_lds[];
   typedef const Item __attribute__((address_space(4)))* ItemRef;
   const ItemRef ip = (ItemRef)(items + blockIdx.x);
@@ -255,16 +255,20 @@ static int item_lanes(int ng) {
   while (lpc * 2 < ng) lpc <<= 1;
   return lpc;
 }
+template <bool FULL>
 static size_t item_lds(int lpc) {
   switch (lpc) {
-    case 1: return sizeof(BlockLds<2, 1>);
-    case 2: return sizeof(BlockLds<2, 2>);
-    case 4: return sizeof(BlockLds<2, 4>);
-    case 8: return sizeof(BlockLds<2, 8>);
-    case 16: return sizeof(BlockLds<2, 16>);
-    case 32: return sizeof(BlockLds<2, 32>);
-    default: return sizeof(BlockLds<2, 64>);
+    case 1: return sizeof(BlockLds<2, 1, FULL>);
+    case 2: return sizeof(BlockLds<2, 2, FULL>);
+    case 4: return sizeof(BlockLds<2, 4, FULL>);
+    case 8: return sizeof(BlockLds<2, 8, FULL>);
+    case 16: return sizeof(BlockLds<2, 16, FULL>);
+    case 32: return sizeof(BlockLds<2, 32, FULL>);
+    default: return sizeof(BlockLds<2, 64, FULL>);
   }
+}
+static int item_threads(bool full) {
+  return full ? block_threads<2, true>() : block_threads<2, false>();
 }
 
 using ItemsFn = void (*)(const KArgs*, const Item*);
@@ -369,13 +373,20 @@ static int build_items(mgrhd_batch* bt) {
   // items of 64 groups.
   const bool rounds = bt->scope == 1 && bt->groups_per_lane == 2;
   constexpr int64_t kLeastRounds = 2;
-  auto in_flight = [](int32_t ng) { return (int64_t)(kBlock / item_lanes(ng)); };
+  auto in_flight = [](int32_t ng) {
+    const int lanes = item_lanes(ng);
+    return (int64_t)(item_threads(2 * lanes == ng) / lanes);
+  };
   int64_t left[2] = {0, 0};  // rounds left of the full items and of the others
   for (int32_t p : order) {
     const KArgs& a = bt->h_patches[p];
     left[full(p)] += (a.n + in_flight(a.ng) - 1) / in_flight(a.ng);
   }
-  const int64_t resident = (int64_t)device_cus() * 4;
+  // workgroups on the chip: four waves per SIMD of the full items, three of the others
+  auto resident = [](bool full) {
+    return (int64_t)device_cus() * (full ? 16 : 12) * kWave / item_threads(full);
+  };
+  const int64_t on_chip[2] = {resident(false), resident(true)};
   for (int32_t p : order) {
     const int64_t n = bt->h_patches[p].n;
     const int32_t ng = bt->h_patches[p].ng;
@@ -384,7 +395,7 @@ static int build_items(mgrhd_batch* bt) {
     for (int64_t c0 = 0; c0 < n;) {
       int64_t cells = bt->chunk;
       if (rounds) {
-        const int64_t r = std::max(left[full(p)] / (2 * resident), kLeastRounds);
+        const int64_t r = std::max(left[full(p)] / (2 * on_chip[full(p)]), kLeastRounds);
         cells = std::min(r * in_flight(ng),
                          std::max<int64_t>(bt->chunk * 32 / item_lanes(ng), 1));
         left[full(p)] -= (std::min(cells, n - c0) + in_flight(ng) - 1) / in_flight(ng);
@@ -395,7 +406,7 @@ static int build_items(mgrhd_batch* bt) {
     }
     bt->ng_items.back().second.second = (int64_t)items.size();
     size_t& lds = full(p) ? bt->lds_full : bt->lds_rest;
-    lds = std::max(lds, item_lds(item_lanes(ng)));
+    lds = std::max(lds, full(p) ? item_lds<true>(item_lanes(ng)) : item_lds<false>(item_lanes(ng)));
     if (full(p)) bt->n_full = (int64_t)items.size();
   }
   if (bt->d_items) (void)hipFree(bt->d_items);
@@ -607,7 +618,7 @@ static int enqueue_items(const mgrhd_batch* bt, hipStream_t stream, bool full, i
       hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)kCuLds) != hipSuccess)
     return MGRHD_E_DEVICE;
-  hipLaunchKernelGGL(fn, dim3((unsigned)(hi - lo)), dim3(kBlock), lds, stream,
+  hipLaunchKernelGGL(fn, dim3((unsigned)(hi - lo)), dim3(item_threads(full)), lds, stream,
                      (const KArgs*)bt->d_patches, (const Item*)(bt->d_items + lo));
   const hipError_t err = hipGetLastError();
   return err == hipSuccess ? 0 : (int)err;

@@ -171,6 +171,19 @@ __device__ __forceinline__ void copy_through(const KArgs& a, const StatePtrs& p,
 }
 
 constexpr int kBlock = 256;
+// Threads of a workgroup: the kernels of two groups per lane without per-slot
+// checks, four waves per SIMD, take 512, two workgroups per CU.  The cells in
+// flight in a workgroup lie together, and a line of a row holds 16 cells: with
+// 16 in flight at 64 groups instead of 8, a line is used by more cells before
+// the L2 drops it (2^24 cells x 64 groups 135 -> 129 ms, 2^21 x 64 17.2 -> 16.1,
+// 2^21 x 16 3.82 -> 3.72; 1024 threads 127, 16.1 and 3.75 ms, but one workgroup
+// per CU then waits for its last cell).  The others hold three waves per SIMD,
+// of which 512 threads would leave one empty, or are small launches, which 512
+// threads would leave on half of the CUs.
+template <int G, bool FULL>
+constexpr int block_threads() {
+  return FULL && G == 2 ? 512 : kBlock;
+}
 constexpr int kWave = 64;
 constexpr double kThird = 1.0 / 3.0;
 
@@ -351,14 +364,15 @@ __device__ __forceinline__ bool stage_tables(const KArgs& a, Tables<NGM>& t) {
 // per-cell constants 1/tau_g = 1/(c_hat dt chi_0E,g) and 1/J_gg of eq. matrix
 // (2G), and with KEEP0 the old-time fluxes F^(t) (3G) that every outer stage
 // needs (without KEEP0 they are re-read from HBM).  Slot s of thread t lives
-// at lds[s * kBlock + t]: the 64 lanes of a wave touch 64 consecutive words,
+// at lds[s * BLK + t]: the 64 lanes of a wave touch 64 consecutive words,
 // free of bank conflicts.  Per-cell values (with KEEP0 the old-time velocity
 // v^(t)) live once per cell, not once per lane: field f of cell slot c at
-// cells[f * CPB + c], CPB the most cells a workgroup holds at once (kBlock /
-// lanes per cell, or kBlock where the lane count varies between waves); all
+// cells[f * CPB + c], CPB the most cells a workgroup holds at once (BLK /
+// lanes per cell, or BLK where the lane count varies between waves); all
 // lanes of a cell read the same word (an LDS broadcast).
-template <int G, bool KEEP0, int CPB = kBlock, bool CONST_AT_USE = false>
+template <int G, bool KEEP0, int CPB = kBlock, bool CONST_AT_USE = false, int BLK = kBlock>
 struct LaneStore {
+  static constexpr int kThreads = BLK;
   static constexpr bool kKeep0 = KEEP0;
   static constexpr int kSlots = 5 * G + (KEEP0 ? 3 * G : 0);
   static constexpr int kCPB = CPB;
@@ -387,11 +401,11 @@ struct LaneStore {
     else
       return a.*m;
   }
-  __device__ __forceinline__ double& F(int d, int k) const { return base[(d * G + k) * kBlock]; }
-  __device__ __forceinline__ double& itau(int k) const { return base[(3 * G + k) * kBlock]; }
-  __device__ __forceinline__ double& iJgg(int k) const { return base[(4 * G + k) * kBlock]; }
+  __device__ __forceinline__ double& F(int d, int k) const { return base[(d * G + k) * BLK]; }
+  __device__ __forceinline__ double& itau(int k) const { return base[(3 * G + k) * BLK]; }
+  __device__ __forceinline__ double& iJgg(int k) const { return base[(4 * G + k) * BLK]; }
   __device__ __forceinline__ double& F0(int d, int k) const {
-    return base[(5 * G + d * G + k) * kBlock];
+    return base[(5 * G + d * G + k) * BLK];
   }
   __device__ __forceinline__ double& v0(int d) const { return cells[d * CPB]; }
 };
@@ -1071,10 +1085,10 @@ __device__ __forceinline__ void run_cells(const KArgs& a, const Tables<NGM>& tab
   static_assert(LPC >= 1 && LPC <= kWave && (LPC & (LPC - 1)) == 0, "lanes per cell");
   const int j = lane % LPC;
   // this cell's slot in the per-cell area: with room for a cell per lane
-  // (CPB = kBlock, the batched kernels, whose waves may run different lane
+  // (CPB = BLK, the batched kernels, whose waves may run different lane
   // counts) the slot of the cell's first lane, else the cell's rank in the
   // workgroup (every wave runs the same lane count)
-  const LS ls = ls_block.at_cell(LS::kCPB == kBlock ? (int)threadIdx.x - j
+  const LS ls = ls_block.at_cell(LS::kCPB == LS::kThreads ? (int)threadIdx.x - j
                                                     : (int)threadIdx.x / LPC);
   CellState<G> s;
   s.phase = P_EMPTY;

@@ -13,11 +13,12 @@ namespace mgrhd {
 // LDS of one workgroup of the state machine with LPC lanes per cell: the group
 // tables, the per-lane slots, the per-cell area, and the cells of the
 // workgroup's range handed out so far.  AT_USE: LaneStore's CONST_AT_USE.
-template <int G, int LPC, bool AT_USE = false>
+template <int G, int LPC, bool FULL, bool AT_USE = false>
 struct BlockLds {
-  using LS = LaneStore<G, true, kBlock / LPC, AT_USE>;
+  static constexpr int kThreads = block_threads<G, FULL>();
+  using LS = LaneStore<G, true, kThreads / LPC, AT_USE, kThreads>;
   Tables<G * LPC> tab;
-  double lane[LS::kSlots * kBlock];
+  double lane[LS::kSlots * kThreads];
   double cell[LS::kCellWords];
   int taken;
 };
@@ -27,16 +28,16 @@ struct BlockLds {
 // block that a was read from.
 template <int G, int LPC, int MODE, bool TD, bool FULL, bool AT_USE>
 __device__ __forceinline__ void run_block(const KArgs& a, KArgsRef ap, int64_t lo, int64_t hi,
-                                          BlockLds<G, LPC, AT_USE>& lds) {
+                                          BlockLds<G, LPC, FULL, AT_USE>& lds) {
   constexpr int NGM = G * LPC;
-  using LS = typename BlockLds<G, LPC, AT_USE>::LS;
+  using LS = typename BlockLds<G, LPC, FULL, AT_USE>::LS;
   const LS ls{lds.lane + threadIdx.x, lds.cell, ap};
   if (threadIdx.x == 0) lds.taken = 0;
   const bool table_ok = stage_tables<NGM, MODE>(a, lds.tab);  // (its barriers publish `taken`)
 
   if (!table_ok) {
     // the table is unusable: report every cell of this workgroup's range
-    for (int64_t i = lo + threadIdx.x; i < hi; i += kBlock) {
+    for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
       copy_through(a, state_ptrs(ap), i, 0, 1);
       if (a.status) a.status[i] = MGRHD_ST_BAD_TABLE;
       if (a.iters) a.iters[i] = 0;
@@ -58,9 +59,9 @@ __device__ __forceinline__ void run_block(const KArgs& a, KArgsRef ap, int64_t l
 // cells x 16 groups 4.35 -> 4.00 ms, PPL-free 5% faster; with the checks they
 // would spill: 11 groups 1.19 -> 1.47 ms).
 template <int G, int LPC, int MODE, int WPE, bool TD, bool FULL>
-__global__ __launch_bounds__(kBlock, FULL && G == 2 && WPE < 4 ? 4 : WPE) void k_source_update(
-    KArgs a) {
-  __shared__ BlockLds<G, LPC> lds;
+__global__ __launch_bounds__((block_threads<G, FULL>()), FULL && G == 2 && WPE < 4 ? 4 : WPE) void
+k_source_update(KArgs a) {
+  __shared__ BlockLds<G, LPC, FULL> lds;
   // the arguments as the device reads them in place (a is the only argument)
   const KArgsRef ap = (KArgsRef)__builtin_amdgcn_kernarg_segment_ptr();
   // each workgroup owns a contiguous range of cells, shared by its waves

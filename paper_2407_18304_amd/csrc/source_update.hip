@@ -102,11 +102,15 @@ static Variant* choose_variant(int ng) {
 }
 
 // resident workgroups per CU of a variant (queried once)
+static int variant_threads(const Variant* v, int full) {
+  return full && v->g == 2 ? block_threads<2, true>() : kBlock;
+}
 static int resident_blocks(Variant* v, int td, int full, int mode) {
   std::lock_guard<std::mutex> lk(g_mutex);
   int& nb = v->blocks_per_cu[td][full][mode];
   if (nb == 0) {
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, v->fn[td][full][mode], kBlock, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, v->fn[td][full][mode],
+                                                     variant_threads(v, full), 0) !=
             hipSuccess ||
         nb < 1)
       nb = 1;
@@ -129,18 +133,20 @@ static int num_cus() {
 
 // The variant of a launch of n cells.  A launch that leaves the chip part empty
 // takes as long as its slowest cell, and a lane with one group has half of a
-// step's work: 4096 cells x 4 groups 64.8 -> 48.7 us, 500 x 16 62.3 -> 40.8,
-// 2048 x 64 56.5 -> 46.9.  The lines, in quarters of the lanes that the chip
-// holds at four waves per SIMD:
-// * 3 where the groups fill the lanes (16384 x 16, all of them, 77.9 -> 74.0
-//   us, but 65536 x 4 81.6 -> 87.9) or the opacity depends on temperature (per
-//   cell it costs two more functions in every lane: 50000 x 5 227 -> 244 us);
+// step's work (4096 cells x 4 groups 59 -> 45 us, 500 x 16 48 -> 36, 2048 x 64
+// 56 -> 45).  The lines, in quarters of the lanes that the chip holds at four
+// waves per SIMD, two groups per lane -> one:
+// * 7 where the groups fill the lanes, PC 6 (57500 x 8 118 -> 113 us, 6144 x 64
+//   84 -> 79, but 65536 x 8 122 -> 123, 8192 x 64 88 -> 97; PC 6144 x 64 77 ->
+//   74, but 7187 x 64 79 -> 84);
+// * 5 where the opacity depends on temperature, which costs two more functions
+//   per cell in every lane (20480 x 16 246 -> 223 us, but 32768 x 16 257 -> 297);
 // * 8 where they leave lanes of both splits empty, since the kernels with the
 //   per-slot checks hold a third more waves at one group per lane (30011 x 11
-//   103.1 -> 94.6 us, but 125000 x 5 201 -> 213);
-// * PPL-free holds more of them still: 16 where the groups fill the lanes
-//   (62500 x 16 829 -> 706 us, but 125000 x 64 2650 -> 2775), always where they
-//   do not (2^19 x 11 5.18 -> 4.56 ms).
+//   122 -> 107 us, but 125000 x 5 201 -> 213);
+// * PPL-free holds more of them still: 14 where the groups fill the lanes (43750
+//   x 16 411 -> 352 us, but 15625 x 64 322 -> 340), always where they do not
+//   (2^19 x 11 3.49 -> 3.05 ms).
 // A variant set by the caller is kept.
 static Variant* launch_variant(int ng, int mode, bool td, int64_t n) {
   Variant* v = choose_variant(ng);
@@ -149,9 +155,8 @@ static Variant* launch_variant(int ng, int mode, bool td, int64_t n) {
   while (lpc < ng) lpc <<= 1;
   const bool full = v->lpc * v->g == ng;
   const int64_t quarter = (int64_t)num_cus() * kBlock;
-  int64_t most = 3 * quarter;
-  if (!full && !td) most = 8 * quarter;
-  if (mode == MGRHD_MEAN_PPL_FREE && !td) most = full ? 16 * quarter : INT64_MAX;
+  int64_t most = (td ? 5 : !full ? 8 : mode == MGRHD_MEAN_PC ? 6 : 7) * quarter;
+  if (mode == MGRHD_MEAN_PPL_FREE && !td) most = full ? 14 * quarter : INT64_MAX;
   Variant* one = n <= most / lpc ? find_variant(lpc, 1, 0) : nullptr;
   return one ? one : v;
 }
@@ -160,15 +165,18 @@ static Variant* launch_variant(int ng, int mode, bool td, int64_t n) {
 // are in flight in a workgroup, resident workgroups on the chip.  Ranges do
 // not get shorter than twice the cells in flight, which would be mostly
 // draining; cells for fewer than four of those per resident workgroup are
-// dealt in one round of equal ranges.  A region is an odd number of lines long,
+// dealt in one round of equal ranges, as many workgroups on every CU, down to a
+// wave on each (500 cells x 16 groups 40.8 -> 36.4 us, 1000 x 4 49.5 -> 42.5, 12288
+// x 32 99 -> 97).  A region is an odd number of lines long,
 // so that the regions of a power-of-two grid start at different sets of the
 // caches (2^21 cells x 16 groups 4.60 -> 3.97 ms).
 static int64_t plan_blocks(KArgs& a, int64_t in_flight, int64_t resident) {
   const int64_t n = a.n;
   a.least = (int32_t)(2 * in_flight);
   if (n <= 4 * a.least * resident) {
-    const int64_t most = (n + in_flight - 1) / in_flight;
-    const int64_t blocks = most < resident ? most : resident;
+    const int64_t cus = num_cus();
+    const int64_t per_cu = (n + in_flight * cus - 1) / (in_flight * cus);
+    const int64_t blocks = std::min(std::min(per_cu * cus, resident), n);
     a.region = a.first = (n + blocks - 1) / blocks;
     a.regions = INT32_MAX;
     return (n + a.region - 1) / a.region;
@@ -340,8 +348,9 @@ int mgrhd_source_update(double* E_g, double* F_g, const double* rho, double* e_g
   const int full = var->lpc * var->g == ng ? 1 : 0;  // every slot holds a group
   const int64_t resident =
       (int64_t)num_cus() * resident_blocks(var, td, full, op->mean_mode);
-  const int64_t blocks = plan_blocks(a, kBlock / var->lpc, resident);
-  hipLaunchKernelGGL(var->fn[td][full][op->mean_mode], dim3((unsigned)blocks), dim3(kBlock), 0,
+  const int threads = variant_threads(var, full);
+  const int64_t blocks = plan_blocks(a, threads / var->lpc, resident);
+  hipLaunchKernelGGL(var->fn[td][full][op->mean_mode], dim3((unsigned)blocks), dim3(threads), 0,
                      (hipStream_t)stream, a);
   const hipError_t err = hipGetLastError();
   return err == hipSuccess ? 0 : (int)err;

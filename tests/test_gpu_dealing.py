@@ -44,8 +44,8 @@ def one_split():
     mgrhd.set_variant(64, 0, 0)
 
 
-# 64 groups: 8 cells in flight in a workgroup, up to 1024 workgroups at once,
-# so that several rounds begin beyond 4 x 16 x 1024 cells (fewer where fewer
+# 64 groups: 16 cells in flight in a workgroup, up to 512 workgroups at once,
+# so that several rounds begin beyond 4 x 32 x 512 cells (fewer where fewer
 # workgroups fit); sizes at that edge, off any multiple, and a power of two
 @pytest.mark.parametrize("n", [49151, 49153, 65535, 65536, 65537, 100003, 131072])
 def test_rounds_of_ranges(n, one_split):
@@ -96,14 +96,16 @@ def test_items_of_a_workgroup(chunk, blocks_per_cu):
 
 
 # launches around the sizes at which a cell's groups are split over more lanes
-# (three quarters of, and twice, the lanes that 256 compute units
-# hold; PPL-free four times),
-# against a split set for every size: groups that fill the lanes and that do not
+# (one and a half, one and three quarters, and two times the lanes that 256
+# compute units hold;
+# PPL-free three and a half times), and of a few cells, against a split set for
+# every size: groups that fill the lanes and that do not
 @pytest.mark.parametrize("ng,split,n,mode", [
-    (4, (2, 2), 49152, 1), (4, (2, 2), 49153, 1), (16, (8, 2), 12288, 0),
-    (16, (8, 2), 12289, 0), (64, (32, 2), 3072, 1), (64, (32, 2), 3073, 1), (3, (2, 2), 7, 1),
+    (4, (2, 2), 114688, 1), (4, (2, 2), 114689, 1), (16, (8, 2), 24576, 0),
+    (16, (8, 2), 24577, 0), (64, (32, 2), 7168, 1), (64, (32, 2), 7169, 1), (3, (2, 2), 7, 1),
     (1, (1, 4), 1, 1), (2, (1, 4), 130, 0), (33, (32, 2), 8192, 1), (33, (32, 2), 8193, 1),
-    (64, (32, 2), 16384, 2), (64, (32, 2), 16385, 2), (23, (16, 2), 5000, 2)])
+    (64, (32, 2), 14336, 2), (64, (32, 2), 14337, 2), (23, (16, 2), 5000, 2),
+    (16, (8, 2), 255, 1), (16, (8, 2), 257, 1), (64, (32, 2), 4097, 0)])
 def test_split_of_a_small_launch(ng, split, n, mode):
     edges = W.log_edges(1e-3, 1e3, ng)
     layout = W.PatchLayout(0, n, ng, 0, edges, edges[:-1] ** -2.0,
