@@ -101,3 +101,23 @@ def test_graph_replay_equals_eager_steps():
     sa, sb = a.state(), b.state()
     for k in ("E_g", "F_g", "e_gas", "v"):
         assert np.array_equal(sa[k], sb[k]), k
+
+
+def test_status_rows_are_folded():
+    """status_any holds the bits of every update since the start, whatever the
+    number of rows that wait for the fold: planted bits in each row of 1 ... 9
+    used ones, and the last update's own bits stay readable."""
+    col = column1d.Column1D(W.marshak(4, n_cells=40), 1)
+    for k in range(1, 10):
+        col.status_any.zero_()
+        col._rows.fill_(64)                      # rows not in use are not folded
+        rows = [torch.randint(0, 64, (40,), dtype=torch.int32, device="cuda") for _ in range(k)]
+        want = torch.zeros_like(col.status_any)
+        for j, r in enumerate(rows):
+            col._rows[j] = r
+            want |= r
+        col._used, col._last = k, k - 1
+        col._fold()
+        assert torch.equal(col.status_any, want), k
+        assert torch.equal(col.status, rows[-1])
+        assert col._used == 0
