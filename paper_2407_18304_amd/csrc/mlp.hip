@@ -5,7 +5,8 @@
 // the fallback and decides the result (the solver converges to the same root
 // whatever the guess).
 //
-// All tensors are FP32 in HBM; every matrix product runs on the gfx950 matrix
+// Parameters, moments and the layer-by-layer path's tensors are FP32 in HBM
+// (mlp_train.hpp has its own BF16 buffers); every matrix product runs on the gfx950 matrix
 // cores as BF16 x BF16 -> FP32 (v_mfma_f32_16x16x32_bf16): operands are
 // rounded to BF16 when a 64x32 / 32x64 tile is staged in LDS, accumulation is
 // FP32.  Master weights and Adam moments are FP32.

@@ -13,15 +13,16 @@
 // the LPC lanes (DPP where the distance fits a row), so every lane of a cell
 // holds bit-identical scalars and takes the same branches.
 //
-// Persistent state machine.  Each workgroup owns a contiguous range of cells,
-// which its waves take through a counter in LDS.  One
-// trip of the main loop performs exactly one material evaluation (G Planck
+// Persistent state machine.  A workgroup's waves take the cells of its range
+// (one of several, shorter from round to round: block_range) through a counter
+// in LDS.  One trip of the main loop performs one material evaluation (G Planck
 // edges, one edge handed over from a neighbour lane, and G group means per
 // lane) for every active cell group, followed by
 // the consumer of the cell's phase: a Newton step, or the flux/momentum
-// update of the outer stage.  The flux-stage evaluation is also the first
-// evaluation of the next inner pass (the pass restarts at the same
-// temperature).  A cell group whose cell has finished takes the next cell of
+// update of the outer stage (where a wave holds one or two cells, by all
+// consumers that the evaluation serves: run_cells).  The flux-stage evaluation
+// is also the first evaluation of the next inner pass (the pass restarts at the
+// same temperature).  A cell group whose cell has finished takes the next cell of
 // the workgroup's range at the top of the next trip, so cells that converge
 // early free their lanes instead of idling until the slowest cell of the wave
 // is done.
@@ -90,9 +91,10 @@ static Variant* choose_variant(int ng) {
     Variant* v = find_variant(g_override_lpc[ng], g_override_g[ng], g_override_wpe[ng]);
     if (v && v->lpc * v->g >= ng) return v;
   }
-  // default: 2 groups per lane at 3 waves per SIMD and enough lanes to cover
-  // N_g (the fastest on gfx950 at 16 and 64 groups); 4 groups per lane where
-  // no 2-group variant covers N_g
+  // default: 2 groups per lane and enough lanes to cover N_g (the fastest on
+  // gfx950 at 16 and 64 groups), at 3 waves per SIMD or at 4 where the groups
+  // fill the lanes (solver_kernel.hpp); 4 groups per lane where no 2-group
+  // variant covers N_g
   int lpc = 1;
   while (lpc * 2 < ng) lpc <<= 1;
   if (Variant* v = find_variant(lpc, 2, 0)) return v;
@@ -135,7 +137,8 @@ static int num_cus() {
 // takes as long as its slowest cell, and a lane with one group has half of a
 // step's work (4096 cells x 4 groups 59 -> 45 us, 500 x 16 48 -> 36, 2048 x 64
 // 56 -> 45).  The lines, in quarters of the lanes that the chip holds at four
-// waves per SIMD, two groups per lane -> one:
+// waves per SIMD, two groups per lane -> one (each taken with one evaluation
+// per step; where a wave holds one or two cells run_cells saves 5 to 10% more):
 // * 7 where the groups fill the lanes, PC 6 (57500 x 8 118 -> 113 us, 6144 x 64
 //   84 -> 79, but 65536 x 8 122 -> 123, 8192 x 64 88 -> 97; PC 6144 x 64 77 ->
 //   74, but 7187 x 64 79 -> 84);

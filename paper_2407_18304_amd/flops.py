@@ -8,7 +8,8 @@ method as the kernels write it, per cell, in FLOP-equivalents:
 * +, -, x = 1 and fused multiply-add = 2; comparisons, selects, integer and
   memory work = 0;
 * a call of exp, expm1, log, sqrt, a division or the kernels' own e^{-x},
-  range-bounded reciprocal and square root (exp_neg, rcp_nr, sqrt_1_4 of
+  e^{-x} with 1 - e^{-x}, logarithm, range-bounded reciprocal, quotient and
+  square root (exp_neg, one_minus_exp, log_pos, rcp_nr, div_nr, sqrt_1_4 of
   planck_device.hpp) costs the FLOP-equivalents of
   the FP64 instruction sequence gfx950 code uses for it (FMA = 2, every other
   FP64 arithmetic instruction = 1, compares 0), counted in the assembly of a
@@ -40,15 +41,16 @@ CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 
 # FLOP-equivalents of one call on gfx950 (measured by measure_weights())
 W = {"exp": 29, "expm1": 34, "log": 84, "div": 17, "sqrt": 19, "exp_neg": 34, "rcp_nr": 9,
-     "sqrt_1_4": 17}
+     "sqrt_1_4": 17, "div_nr": 14, "log_pos": 42, "one_minus_exp": 38}
 
 PC, FIXED, FREE = 0, 1, 2
 
 
 def unit_costs(w=W):
     """Per-unit FLOP-equivalents of the kernel source (see module doc)."""
-    e, m1, lg, dv, sq = w["exp"], w["expm1"], w["log"], w["div"], w["sqrt"]
+    e, dv = w["exp"], w["div"]
     en, rc, s14 = w["exp_neg"], w["rcp_nr"], w["sqrt_1_4"]
+    dn, lp, om = w["div_nr"], w["log_pos"], w["one_minus_exp"]
     # one Planck edge: x = hk/T * nu (1), x^2 and x^3 (2), then by branch
     edge_common = 1 + 2
     poly_P = 14 * 2 + 6              # degree-14 Horner in x^2 and the bracket
@@ -56,29 +58,29 @@ def unit_costs(w=W):
     edge = {
         "x<=2": edge_common + poly_P + poly_E,
         "2<x<=4": edge_common + poly_P + poly_E,
-        # e^{-x}, the 10-term tail as four degree-9 Horner chains in u and their
-        # combination, then x^4/(1 - u) (three products, 1 - u, a reciprocal)
-        "x>4": edge_common + en + 4 * 9 * 2 + 10 + (4 + rc),
+        # e^{-x}, the tail as four Horner chains in u of 9, 9, 8 and 7 terms and
+        # their combination, then x^4/(1 - u) (three products, 1 - u, a reciprocal)
+        "x>4": edge_common + en + (8 + 8 + 7 + 6) * 2 + 10 + (4 + rc),
         # the lowest edge at x <= 0.1: both polynomials truncated to degree 3
         "low": edge_common + 2 * (3 * 2 + 6),
     }
     # group data from its two edges (group_planck)
-    group = {"both<=4": 1, "straddle": 4, "wien": 3 + dv}
+    group = {"both<=4": 1, "straddle": 4, "wien": 3 + dn}
     # per group and evaluation, after the Planck data: B~, Delta(nu B~), dB/dT (8)
     ev_group = {
         PC: 1 + 8 + 3,                                        # chi (1), emit
-        FIXED: 1 + 8 + 4 + 4 + 3 + dv + 5,                    # chi, dchib, chi_F num/den, emit
+        FIXED: 1 + 8 + 4 + 4 + 3 + dn + 5,                    # chi, dchib, chi_F num/den, emit
         # E_g of the iterate (1), logs of the two slope fits (B and E), two
-        # slope pairs, two group means (two expm1-brackets, a division and a
-        # rescaling exp each), chi_F, emit
-        FREE: 1 + 8 + 1 + (2 * lg + 3) + 2 * (2 * (2 + dv)) +
-              2 * (1 + 1 + 2 * (2 + m1 + dv) + 3 + dv + e) + 3 + 6 + 3 + dv + 5,
+        # slope pairs, two group means (the two exponents 5, two exponentials,
+        # a reciprocal, five products), chi_F, emit
+        FREE: 1 + 8 + 1 + (2 * lp + 3) + 2 * (2 * 2) +
+              2 * (1 + 5 + 2 * om + rc + 5) + 3 + 6 + 3 + dn + 5,
     }
     ev_cell = 2 + 3 + dv + 1           # T = (E_gas - ke)/(rho c_v) (2), a T^4, 1/T, hk/T
     # Newton step per group: W (5, with v.F cached per pass), E_g (3), F_R (2),
     # J_g0 (1), a_g b_g (2), four sums (4), update of R_g (4); PPL-free adds
-    # chi_B/chi_E and its two products, 1/tau (1 + div) and 1/J_gg (1 + rcp)
-    nt_group = {PC: 21, FIXED: 21, FREE: 21 + 2 + dv + (1 + dv) + (1 + rc)}
+    # chi_B/chi_E and its two products, 1/tau and 1/J_gg (1 + rcp each)
+    nt_group = {PC: 21, FIXED: 21, FREE: 21 + 2 + dn + (1 + rc) + (1 + rc)}
     # per cell: F_G (3), the two stop tests (3), dx_0 (numerator and
     # denominator 4, a division by a reciprocal and one correction: rc + 5),
     # the positivity check of the step (3), the update of E_gas (2)
@@ -103,16 +105,16 @@ def unit_costs(w=W):
     # beyond.  Per group: chi_0,g- at T (2 products, 3 with the factor); with
     # the factor in PPL, the ratio s_g+/s_g-, the index change ln(ratio)/ln r,
     # r^alpha times the ratio, and in PPL-fixed the mean of eq. chiQg at the
-    # new index (a y = aL, an expm1-bracket, a division, the rescaling exp of
-    # half the groups, the product).  Per Newton step and group: 1/tau and
+    # new index (y = aL + ln(ratio), an exponential, a reciprocal, three
+    # products).  Per Newton step and group: 1/tau and
     # 1/J_gg (no longer per-cell constants); the cell load skips them.
     td = dict(
-        ev_cell_pow=1 + lg + e + 1,
-        edge_stim={"nonwien": 1 + dv, "wien": 1},
+        ev_cell_pow=1 + lp + e + 1,
+        edge_stim={"nonwien": 2 + rc, "wien": 1},
         ev_group={PC: 2, FIXED: 3, FREE: 2},
-        ev_group_stim={PC: 1, FIXED: 1 + dv + lg + dv + 1 + 1 + (1 + m1 + dv) + dv + e / 2,
-                       FREE: 1 + dv + lg + dv + 1 + 1},
-        nt_group={PC: (1 + dv) + (1 + rc), FIXED: (1 + dv) + (1 + rc), FREE: 0},
+        ev_group_stim={PC: 1, FIXED: 1 + (1 + rc) + lp + (2 + rc) + 1 + 2 + (om + rc + 3),
+                       FREE: 1 + (1 + rc) + lp + (2 + rc) + 1},
+        nt_group={PC: 2 * (1 + rc), FIXED: 2 * (1 + rc), FREE: 0},
         ld_group={PC: -((2 + dv) + (1 + rc)), FIXED: -((2 + dv) + (1 + rc)), FREE: 0},
     )
     return dict(edge=edge, group=group, ev_group=ev_group, ev_cell=ev_cell,
@@ -125,7 +127,7 @@ UNIT = unit_costs()
 # reciprocal and square root included) as one operation, transcendentals as
 # above: the lower figure a convention that prices only exp/expm1/log by their
 # instruction sequences gives.
-UNIT_DIV_SQRT_1 = unit_costs(dict(W, div=1, sqrt=1, rcp_nr=1, sqrt_1_4=1))
+UNIT_DIV_SQRT_1 = unit_costs(dict(W, div=1, sqrt=1, rcp_nr=1, sqrt_1_4=1, div_nr=1))
 
 
 def edge_mix(nu, hk, T):
@@ -204,6 +206,9 @@ K(p_sqrt, sqrt(x))
 K(p_exp_neg, mgrhd::exp_neg(x))
 K(p_rcp_nr, mgrhd::rcp_nr(x))
 K(p_sqrt_1_4, mgrhd::sqrt_1_4(x))
+K(p_div_nr, mgrhd::div_nr(a[i + 64], x))
+K(p_log_pos, mgrhd::log_pos(x))
+K(p_one_minus_exp, o[i + 64] = mgrhd::one_minus_exp(x).e; o[i] = mgrhd::one_minus_exp(x).em)
 """
 
 
