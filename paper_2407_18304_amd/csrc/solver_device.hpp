@@ -1144,32 +1144,12 @@ __device__ __forceinline__ void run_cells(const KArgs& a, const Tables<NGM>& tab
     evaluate<G, LPC, MODE, NGM, TD>(tab, group_count<G, LPC, FULL>(a), j, s.lpc, T, aT4,
                                     ls.cst(a, &KArgs::hk), s.rho_kappa, Ecur, c, ot);
 
-    // The polish step and the next pass's first step are taken at a temperature
-    // that the last step moved by rounding alone.  There the terms of this
-    // evaluation stand: B_g is carried on to first order, which leaves an error
-    // of second order (below 1e-25 of B_g), dB/dT an error below 1e-12 of the
-    // Jacobian, and the opacities do not depend on T.  What it saves is half the
-    // evaluations of a small launch, whose time is one cell's serial chain:
-    // 6144 x 64 77.8 -> 69.6 us, 8000 x 51 90.7 -> 83.3, 12000 x 32 83.9 -> 77.8
-    // (PC 78.9 -> 72.4).  With four or more cells to a wave they wait for each
-    // other's consumers instead (16384 x 8 56.7 -> 59.6 us), and with two groups
-    // per lane the loop costs registers that spill (2^21 x 64 16.0 -> 29.6 ms).
-    constexpr bool kStay = G == 1 && LPC >= 32 && MODE != MGRHD_MEAN_PPL_FREE && !TD;
-    for (;;) {
-      if (s.phase == P_FLUX) {
-        if (!flux_step<G, LPC, MODE, NGM, TD, FULL>(a, tab, j, s, ls, c)) break;
-        // the next inner pass starts at this temperature: fall through
-      }
-      if (s.elim) group_balance<G, LPC, MODE, NGM, TD, FULL>(a, tab, j, s, ls, c);
-      newton_step<G, LPC, MODE, NGM, TD, FULL>(a, tab, j, s, ls, c);
-      if (!kStay || (s.phase != P_NEWTON && s.phase != P_FLUX)) break;
-      const double dT = (s.egv - s.ke) * s.ircv - T;
-      if (!(fabs(dT) <= 0x1p-44 * T)) break;
-#pragma unroll
-      for (int k = 0; k < G; ++k)
-        if (gidx<LPC>(j, k, s.lpc) < group_count<G, LPC, FULL>(a))
-          c.Bt[k] = fma(c.dBdT[k], dT, c.Bt[k]);
+    if (s.phase == P_FLUX) {
+      if (!flux_step<G, LPC, MODE, NGM, TD, FULL>(a, tab, j, s, ls, c)) continue;
+      // the next inner pass starts at this temperature: fall through
     }
+    if (s.elim) group_balance<G, LPC, MODE, NGM, TD, FULL>(a, tab, j, s, ls, c);
+    newton_step<G, LPC, MODE, NGM, TD, FULL>(a, tab, j, s, ls, c);
   }
 }
 

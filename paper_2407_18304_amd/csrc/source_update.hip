@@ -19,8 +19,7 @@
 // edges, one edge handed over from a neighbour lane, and G group means per
 // lane) for every active cell group, followed by
 // the consumer of the cell's phase: a Newton step, or the flux/momentum
-// update of the outer stage (where a wave holds one or two cells, by all
-// consumers that the evaluation serves: run_cells).  The flux-stage evaluation
+// update of the outer stage.  The flux-stage evaluation
 // is also the first evaluation of the next inner pass (the pass restarts at the
 // same temperature).  A cell group whose cell has finished takes the next cell of
 // the workgroup's range at the top of the next trip, so cells that converge
@@ -137,8 +136,7 @@ static int num_cus() {
 // takes as long as its slowest cell, and a lane with one group has half of a
 // step's work (4096 cells x 4 groups 59 -> 45 us, 500 x 16 48 -> 36, 2048 x 64
 // 56 -> 45).  The lines, in quarters of the lanes that the chip holds at four
-// waves per SIMD, two groups per lane -> one (each taken with one evaluation
-// per step; where a wave holds one or two cells run_cells saves 5 to 10% more):
+// waves per SIMD, two groups per lane -> one:
 // * 7 where the groups fill the lanes, PC 6 (57500 x 8 118 -> 113 us, 6144 x 64
 //   84 -> 79, but 65536 x 8 122 -> 123, 8192 x 64 88 -> 97; PC 6144 x 64 77 ->
 //   74, but 7187 x 64 79 -> 84);

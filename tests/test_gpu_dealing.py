@@ -105,8 +105,7 @@ def test_items_of_a_workgroup(chunk, blocks_per_cu):
     (16, (8, 2), 24577, 0), (64, (32, 2), 7168, 1), (64, (32, 2), 7169, 1), (3, (2, 2), 7, 1),
     (1, (1, 4), 1, 1), (2, (1, 4), 130, 0), (33, (32, 2), 8192, 1), (33, (32, 2), 8193, 1),
     (64, (32, 2), 14336, 2), (64, (32, 2), 14337, 2), (23, (16, 2), 5000, 2),
-    (16, (8, 2), 255, 1), (16, (8, 2), 257, 1), (64, (32, 2), 4097, 0),
-    (32, (16, 2), 12000, 0), (31, (16, 2), 9000, 1)])
+    (16, (8, 2), 255, 1), (16, (8, 2), 257, 1), (64, (32, 2), 4097, 0)])
 def test_split_of_a_small_launch(ng, split, n, mode):
     edges = W.log_edges(1e-3, 1e3, ng)
     layout = W.PatchLayout(0, n, ng, 0, edges, edges[:-1] ** -2.0,
