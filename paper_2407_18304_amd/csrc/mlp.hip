@@ -865,22 +865,25 @@ static void backward(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld_
   }
 }
 
-// The BF16 copies of the weights brought up to date.  In a capture nothing has
-// run yet, so the copies stay marked as old for calls outside the graph.
 static bool capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
 }
 
+// The BF16 copies of the weights brought up to date.  In a capture nothing has
+// run yet, so the copies stay marked as old for calls outside the graph; and
+// the copies are formed in every graph, whether or not they are old now, as
+// the weights may have changed when it is replayed.
 static void pack_weights(mgrhd_mlp* m, hipStream_t s) {
-  if (!m->dirty) return;
+  const bool graph = capturing(s);
+  if (!m->dirty && !graph) return;
   for (int l = 0; l < 4; ++l)
     hipLaunchKernelGGL(k_pack, grid1((int64_t)m->n_pad[l] * m->k_pad[l]), dim3(256), 0, s,
                        m->params + m->w_off[l], m->params + m->b_off[l], m->out_dim[l],
                        m->in_dim[l], m->n_pad[l], m->k_pad[l], m->wpack + m->wp_off[l],
                        m->bpack + m->bp_off[l], m->wtrans ? m->wtrans + m->wt_off[l] : nullptr,
                        m->kt_pad[l]);
-  m->dirty = capturing(s);
+  m->dirty = graph;
 }
 
 // Gradients of `rows` rows by the three kernels of mlp_train.hpp, into

@@ -335,3 +335,68 @@ def test_training_pass_at_tile_edges(ng, rows):
     other.set_params(a)
     other.gradients(Xd, Td)
     assert np.array_equal(net.get_params(which=1), other.get_params(which=1))
+
+
+def _train_case(net, rows, seed=1):
+    rng = np.random.default_rng(seed)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda()
+    return t(rng.normal(size=(net.n_in, rows))), t(rng.normal(size=(rows, net.n_out)))
+
+
+def _graph_of(fn):
+    g = torch.cuda.CUDAGraph()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(g, stream=s):
+        out = fn()
+    return g, out
+
+
+def _gradients_of(params, like, X, Y):
+    net = warmstart.MLP(like.n_in, like.n_out, 128, max_rows=like.max_rows)
+    net.set_params(params)
+    loss = float(net.gradients(X, Y).cpu())
+    return loss, net.get_params(which=1)
+
+
+def test_captured_gradients_are_those_of_the_present_weights():
+    """A replay of captured gradients after the weights were changed outside
+    the graph (by set_params, by an Adam step, by a training step): the
+    gradients of a network that was given the same weights."""
+    net = _small_net()
+    X, Y = _train_case(net, 96)
+    net.gradients(X, Y)                       # nothing is out of date when the capture begins
+    graph, loss = _graph_of(lambda: net.gradients(X, Y))
+    L = warmstart._lib()
+
+    def adam():
+        assert L.mgrhd_mlp_adam_step(net._h, 1e-2, net._stream()) == 0
+
+    p0 = net.get_params()
+    for change in (lambda: None, adam, lambda: net.set_params(0.5 * p0),
+                   lambda: net.train_step(X, Y, 1e-2), adam):
+        change()
+        torch.cuda.synchronize()
+        graph.replay()
+        got = float(loss.cpu()), net.get_params(which=1)
+        want = _gradients_of(net.get_params(), net, X, Y)
+        assert got[0] == want[0] and np.array_equal(got[1], want[1])
+    eager = float(net.gradients(X, Y).cpu())
+    assert eager == want[0] and np.array_equal(net.get_params(which=1), want[1])
+
+
+def test_captured_training_step_follows_new_weights():
+    """A captured training step replayed after set_params: the step of a
+    network that was given those weights."""
+    net, other = _small_net(), _small_net()
+    X, Y = _train_case(net, 70)
+    net.gradients(X, Y)
+    graph, _ = _graph_of(lambda: net.train_step(X, Y, 1e-2))
+    p = 0.7 * net.get_params()
+    for n in (net, other):
+        n.set_params(p)
+    graph.replay()
+    other.train_step(X, Y, 1e-2)
+    torch.cuda.synchronize()
+    assert np.array_equal(net.get_params(which=1), other.get_params(which=1))
+    assert np.array_equal(net.get_params(), other.get_params())
