@@ -36,26 +36,29 @@ class Column1D:
                     "alpha": t(prob.alpha_chi), "chi_mid": t(prob.chi_mid),
                     "El": t(prob.E_left), "Er": t(prob.E_right)}
         n = prob.n
+        # status bits of the last source update, and of all of them; the
+        # tensors stay the same
+        self.status = torch.zeros(n, dtype=torch.int32, device=dev)
+        self.status_any = torch.zeros(n, dtype=torch.int32, device=dev)
         # a row of status bits per source update, folded into status_any when
         # the rows are used up and at the end of every step() and run(): on a
         # short column an OR per update cost as much as a transport stage (4.4
         # of 20 us per stage at 500 cells x 16 groups)
         self._rows = torch.zeros((max(2, min(1024, (1 << 22) // n)), n), dtype=torch.int32,
                                  device=dev)
-        self._used, self._last = 0, 0
-        self.status_any = torch.zeros(n, dtype=torch.int32, device=dev)
+        self._used, self._last = 0, None   # rows in use; the last update's, if it has one
         self.steps_done = 0
         self.source_kw = source_kw
         self._graph, self._graph_steps = None, 0
 
     # ------------------------------------------------------------------
-    @property
-    def status(self):
-        """Status bits of the last source update, [n]."""
-        return self._rows[self._last]
-
     def _fold(self):
-        """status_any |= the rows used so far, pairwise."""
+        """status = the last update's row, status_any |= the rows used so far,
+        pairwise.  Both on the device, so that a replay leaves what the same
+        steps leave eagerly."""
+        if self._last is not None:
+            row, self._last = self._rows[self._last], None
+            torch.bitwise_or(row, row, out=self.status)
         k, self._used = self._used, 0
         if k == 0:
             return
@@ -65,17 +68,22 @@ class Column1D:
             k -= h
         torch.bitwise_or(self.status_any, self._rows[0], out=self.status_any)
 
-    def _source(self, U, theta_dt):
+    def _source(self, U, theta_dt, status=None):
+        """One source update; its status bits into a row, or into status."""
         p = self.prob
-        if self._used == self._rows.shape[0]:
-            self._fold()
-        self._last = self._used
-        self._used += 1
+        row = None
+        if status is None:
+            if self._used == self._rows.shape[0]:
+                self._fold()
+            row = self._used
+            status = self._rows[row]
         mgrhd.source_update(U["E_g"], U["F_g"], self.U["rho"], U["e_gas"], U["v"],
                             self.tab["edges"], self.tab["chi_lo"], mean_mode=self.mode,
                             alpha_chi=self.tab["alpha"], dt=theta_dt, c_hat=self.c_hat,
-                            polish=self.polish, status=self._rows[self._last], **p.consts(),
-                            **self.source_kw)
+                            polish=self.polish, status=status, **p.consts(), **self.source_kw)
+        self._last = row
+        if row is not None:
+            self._used += 1
 
     def _stage(self, out, U1, U0, a, b, dt_T):
         p = self.prob
@@ -85,16 +93,17 @@ class Column1D:
 
     def step(self):
         """One IMEX step (eager, on the current stream)."""
-        self._step()
+        self._step(self.status)
         self._fold()
+        torch.bitwise_or(self.status_any, self.status, out=self.status_any)
 
-    def _step(self):
+    def _step(self, status=None):
         dt = self.prob.dt
         U, Ut = self.U, self.Ut
         self._stage(Ut, U, None, 0.0, 1.0, dt)          # U^t = U^n + dt T(U^n)
         self._source(Ut, dt)                            # -> U^(n+1/2) in Ut
         self._stage(U, Ut, U, 0.5, 0.5, 0.5 * dt)       # U <- (U^n + U^(n+1/2))/2 + dt/2 T
-        self._source(U, 0.5 * dt)                       # -> U^(n+1) in U
+        self._source(U, 0.5 * dt, status)               # -> U^(n+1) in U
         self.steps_done += 1
 
     def run(self, steps, graph_steps=500):

@@ -121,3 +121,38 @@ def test_status_rows_are_folded():
         assert torch.equal(col.status_any, want), k
         assert torch.equal(col.status, rows[-1])
         assert col._used == 0
+
+
+@pytest.mark.parametrize("calls", [(("run", 60, 50), ("run", 50, 50)),
+                                   (("step",), ("run", 21, 10), ("step",), ("run", 10, 10),
+                                    ("run", 3, 0), ("run", 20, 10)),
+                                   (("run", 1201, 600), ("step",), ("run", 600, 600))])
+def test_status_is_the_last_updates(calls, monkeypatch):
+    """After every call `status` holds the bits of the last update and
+    status_any those of all, replayed as eagerly and in the tensors that a
+    caller took at the start.  The Newton iteration stops at a cap that some
+    cells of some updates reach."""
+    prob = W.marshak(4, n_cells=40)
+    a, b = (column1d.Column1D(prob, 1, max_newton=2, eps_newton=1e-18) for _ in range(2))
+    last, every = a.status, a.status_any
+    update, bits = mgrhd.source_update, []
+
+    def recorded(*args, status, **kw):
+        update(*args, status=status, **kw)
+        bits.append(status.clone())
+
+    want_any = torch.zeros(40, dtype=torch.int32, device="cuda")
+    seen = []
+    for name, *args in calls:
+        getattr(a, name)(*args)
+        with monkeypatch.context() as m:
+            m.setattr(mgrhd, "source_update", recorded)
+            b.run(args[0] if args else 1, graph_steps=0)
+        for r in bits:
+            want_any |= r
+        assert a.steps_done == b.steps_done
+        assert torch.equal(a.status, bits[-1]) and torch.equal(last, bits[-1]), (name, args)
+        assert torch.equal(a.status_any, want_any) and torch.equal(every, want_any), (name, args)
+        seen += [tuple(r.cpu().tolist()) for r in bits]
+        bits.clear()
+    assert len(set(seen)) > 2          # the bits do differ between updates
