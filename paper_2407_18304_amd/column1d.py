@@ -44,7 +44,7 @@ class Column1D:
         # the rows are used up and at the end of every step() and run(): on a
         # short column an OR per update cost as much as a transport stage (4.4
         # of 20 us per stage at 500 cells x 16 groups)
-        self._rows = torch.zeros((max(2, min(1024, (1 << 22) // n)), n), dtype=torch.int32,
+        self._rows = torch.zeros((max(2, min(1024, (1 << 22) // max(n, 1))), n), dtype=torch.int32,
                                  device=dev)
         self._used, self._last = 0, None   # rows in use; the last update's, if it has one
         self.steps_done = 0

@@ -3,6 +3,8 @@ and mgrhd_source_update per stage, paper_2407_18304_amd/column1d.py): the
 transport stage against the oracle's transport operator, and whole IMEX steps
 of the Marshak problem against the oracle's steps, eager and replayed from a
 HIP graph.  GPU only."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -156,3 +158,13 @@ def test_status_is_the_last_updates(calls, monkeypatch):
         seen += [tuple(r.cpu().tolist()) for r in bits]
         bits.clear()
     assert len(set(seen)) > 2          # the bits do differ between updates
+
+
+def test_column_of_no_cells():
+    """A domain that holds no cell takes its steps like any other."""
+    prob = W.marshak(4, n_cells=40)
+    col = column1d.Column1D(dataclasses.replace(
+        prob, n=0, state={k: v[..., :0] for k, v in prob.state.items()}), 1)
+    col.step()
+    col.run(3, graph_steps=0)
+    assert col.steps_done == 4 and col.status_any.numel() == 0 and col.status.numel() == 0
