@@ -392,9 +392,19 @@ void mgrhd_batch_destroy(mgrhd_batch* b);
  * ln(c_hat dt chi_0E,g); outputs (n_out = 1 + N_g): ln(T_new/T),
  * ln(E_g,new/a T^4).  The handle owns its device buffers (allocated once in
  * create for up to max_rows rows per call).  n_hidden and n_out are at most
- * 256 (MGRHD_E_SIZE otherwise).  Weight gradients are summed over row blocks
- * with atomic adds, so gradients (and training) agree between runs to
- * rounding, not bit for bit. */
+ * 256 (MGRHD_E_SIZE otherwise).  With 128 hidden units and at most 416 inputs
+ * the gradients are summed in a fixed order and agree between runs bit for
+ * bit; other networks, and the FP32 checking path, sum weight gradients over
+ * row blocks with atomic adds, so gradients (and training) agree between runs
+ * to rounding.
+ * Streams and graphs: forward, gradients, adam_step and train_step of one
+ * handle share its buffers and must be ordered among themselves.  An inference
+ * reads copies of the weights of its own, which the first inference after the
+ * weights changed forms on its stream; that one must be ordered with the
+ * changes, later ones may run beside training on another stream.  A captured
+ * training call multiplies by the weights at the replay; a captured inference
+ * by the copies as the last inference formed them (in the graph itself, if the
+ * weights had changed since when it was captured). */
 typedef struct mgrhd_mlp mgrhd_mlp;
 int mgrhd_mlp_create(int32_t n_in, int32_t n_hidden, int32_t n_out, int64_t max_rows,
                      uint64_t seed, mgrhd_mlp** out);

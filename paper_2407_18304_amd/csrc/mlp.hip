@@ -745,7 +745,7 @@ struct mgrhd_mlp {
   int64_t n_params = 0;
   int in_dim[kLayers], out_dim[kLayers];
   int64_t w_off[kLayers], b_off[kLayers];
-  void* owned = nullptr;    // params to bpack and wtrans
+  void* owned = nullptr;    // params to the BF16 copies
   float* params = nullptr;  // [n_params] weights (out x in, row-major) then biases
   float* grads = nullptr;
   float* adam_m = nullptr;
@@ -759,17 +759,22 @@ struct mgrhd_mlp {
   float* dY = nullptr;
   float* dA = nullptr;
   float* dB = nullptr;
-  // BF16 copies for the fused inference (repacked when the weights change)
-  __bf16* wpack = nullptr;
-  float* bpack = nullptr;
+  // BF16 copies of the weights, for the fused inference and for the training
+  // kernels each their own: those of the inference change on its own stream
+  // only, so that a training step on another stream leaves an inference that
+  // runs beside it alone
+  struct Copies {
+    __bf16* w = nullptr;   // [n_pad x k_pad] of every layer
+    float* b = nullptr;    // [n_pad]
+    __bf16* wt = nullptr;  // transposes (training)
+    bool old = true;       // the weights have changed since
+  };
+  Copies infer, train;
   int k_pad[kLayers], n_pad[kLayers];
   int64_t wp_off[kLayers], bp_off[kLayers];
-  bool dirty = true;
   bool fp32 = false;  // FP32 operands in the forward and backward products
-  // the three-kernel training pass (128 hidden units, inputs that fit its
-  // tiles): BF16 transposes of the weights, partial sums
+  // the three-kernel training pass (128 hidden units, inputs that fit its tiles)
   bool fused = false;
-  __bf16* wtrans = nullptr;
   float* partial = nullptr;     // [kMaxSplits][n_params] weight gradients
   int kt_pad[kLayers];
   int64_t wt_off[kLayers];
@@ -870,27 +875,26 @@ static bool capturing(hipStream_t s) {
   return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
 }
 
-// The BF16 copies of the weights brought up to date.  In a capture nothing has
-// run yet, so the copies stay marked as old for calls outside the graph; and
-// the copies are formed in every graph, whether or not they are old now, as
-// the weights may have changed when it is replayed.
-static void pack_weights(mgrhd_mlp* m, hipStream_t s) {
-  const bool graph = capturing(s);
-  if (!m->dirty && !graph) return;
+// BF16 copies of the weights brought up to date.  In a capture nothing has run
+// yet, so they stay marked as old for calls outside the graph.
+static void pack_weights(mgrhd_mlp* m, mgrhd_mlp::Copies& c, hipStream_t s) {
+  if (!c.old) return;
   for (int l = 0; l < 4; ++l)
     hipLaunchKernelGGL(k_pack, grid1((int64_t)m->n_pad[l] * m->k_pad[l]), dim3(256), 0, s,
                        m->params + m->w_off[l], m->params + m->b_off[l], m->out_dim[l],
-                       m->in_dim[l], m->n_pad[l], m->k_pad[l], m->wpack + m->wp_off[l],
-                       m->bpack + m->bp_off[l], m->wtrans ? m->wtrans + m->wt_off[l] : nullptr,
-                       m->kt_pad[l]);
-  m->dirty = graph;
+                       m->in_dim[l], m->n_pad[l], m->k_pad[l], c.w + m->wp_off[l],
+                       c.b + m->bp_off[l], c.wt ? c.wt + m->wt_off[l] : nullptr, m->kt_pad[l]);
+  c.old = capturing(s);
 }
 
 // Gradients of `rows` rows by the three kernels of mlp_train.hpp, into
 // m->grads and m->loss (and loss_out); adam: with the step of rate lr.
 static int train_pass(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld_x, int64_t rows,
                       const float* Tgt, float* loss_out, bool adam, float lr) {
-  pack_weights(m, s);
+  // a graph forms the copies itself, whether or not they are old now: the
+  // weights may have changed when it is replayed
+  if (capturing(s)) m->train.old = true;
+  pack_weights(m, m->train, s);
   const int64_t pitch = (rows + kRowTile - 1) / kRowTile * kRowTile;
   const int64_t row_blocks = pitch / kRowTile;
   TrainArgs t;
@@ -910,9 +914,9 @@ static int train_pass(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld
   };
   t.XT = take(m->k_pad[0]);
   for (int l = 0; l < 4; ++l) {
-    t.W[l] = m->wpack + m->wp_off[l];
-    t.WT[l] = m->wtrans + m->wt_off[l];
-    t.b[l] = m->bpack + m->bp_off[l];
+    t.W[l] = m->train.w + m->wp_off[l];
+    t.WT[l] = m->train.wt + m->wt_off[l];
+    t.b[l] = m->train.b + m->bp_off[l];
     t.K_pad[l] = m->k_pad[l];
     t.N_pad[l] = m->n_pad[l];
     t.kt_pad[l] = m->kt_pad[l];
@@ -974,9 +978,9 @@ static int train_pass(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld
     f.out_dim[l] = m->out_dim[l];
     f.K_pad[l] = m->k_pad[l];
     f.kt_pad[l] = m->kt_pad[l];
-    f.W[l] = m->wpack + m->wp_off[l];
-    f.WT[l] = m->wtrans + m->wt_off[l];
-    f.b[l] = m->bpack + m->bp_off[l];
+    f.W[l] = m->train.w + m->wp_off[l];
+    f.WT[l] = m->train.wt + m->wt_off[l];
+    f.b[l] = m->train.b + m->bp_off[l];
   }
   const unsigned blocks =
       (unsigned)(f.n_weight_blocks + (m->n_params - f.n_weights + 7) / 8);
@@ -985,7 +989,8 @@ static int train_pass(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld
     adam_factors(m->step, f.b1, f.b2, f.eps, f.c1, f.c2);
     f.lr = lr;
     hipLaunchKernelGGL(k_train_finish<true>, dim3(blocks), dim3(256), 0, s, f);
-    m->dirty = capturing(s);  // (the copies are written with the weights)
+    m->infer.old = true;
+    m->train.old = capturing(s);  // (its copies are written with the weights)
   } else {
     hipLaunchKernelGGL(k_train_finish<false>, dim3(blocks), dim3(256), 0, s, f);
   }
@@ -1064,9 +1069,11 @@ int mgrhd_mlp_create(int32_t n_in, int32_t n_hidden, int32_t n_out, int64_t max_
   };
   const int64_t at_params = place(off, sizeof(float)), at_grads = place(off, sizeof(float)),
                 at_m = place(off, sizeof(float)), at_v = place(off, sizeof(float)),
-                at_loss = place(1, sizeof(float)), at_bpack = place(btot, sizeof(float)),
-                at_wpack = place(wtot, sizeof(__bf16)),
-                at_wtrans = m->fused ? place(ttot, sizeof(__bf16)) : 0;
+                at_loss = place(1, sizeof(float)), at_b = place(btot, sizeof(float)),
+                at_w = place(wtot, sizeof(__bf16)),
+                at_train_b = m->fused ? place(btot, sizeof(float)) : 0,
+                at_train_w = m->fused ? place(wtot, sizeof(__bf16)) : 0,
+                at_train_wt = m->fused ? place(ttot, sizeof(__bf16)) : 0;
   const int64_t partial = m->fused ? kMaxSplits * off : 0;
   unsigned char* base = nullptr;
   const bool ok =
@@ -1081,10 +1088,12 @@ int mgrhd_mlp_create(int32_t n_in, int32_t n_hidden, int32_t n_out, int64_t max_
     m->adam_m = (float*)(base + at_m);
     m->adam_v = (float*)(base + at_v);
     m->loss = (float*)(base + at_loss);
-    m->bpack = (float*)(base + at_bpack);
-    m->wpack = (__bf16*)(base + at_wpack);
+    m->infer.b = (float*)(base + at_b);
+    m->infer.w = (__bf16*)(base + at_w);
     if (m->fused) {
-      m->wtrans = (__bf16*)(base + at_wtrans);
+      m->train.b = (float*)(base + at_train_b);
+      m->train.w = (__bf16*)(base + at_train_w);
+      m->train.wt = (__bf16*)(base + at_train_wt);
       m->partial = m->act + act;
     }
   }
@@ -1123,7 +1132,7 @@ int mgrhd_mlp_get_params(const mgrhd_mlp* m, float* host, int32_t which) {
 
 int mgrhd_mlp_set_params(mgrhd_mlp* m, const float* host) {
   if (!m || !host) return MGRHD_E_NULL;
-  m->dirty = true;
+  m->infer.old = m->train.old = true;
   return hipMemcpy(m->params, host, sizeof(float) * m->n_params, hipMemcpyHostToDevice) ==
                  hipSuccess
              ? 0 : MGRHD_E_DEVICE;
@@ -1201,7 +1210,7 @@ int mgrhd_mlp_adam_step(mgrhd_mlp* m, float lr, mgrhd_stream_t stream) {
   if (!m) return MGRHD_E_NULL;
   hipStream_t s = (hipStream_t)stream;
   m->step += 1;
-  m->dirty = true;
+  m->infer.old = m->train.old = true;
   float b1, b2, eps, c1, c2;
   adam_factors(m->step, b1, b2, eps, c1, c2);
   hipLaunchKernelGGL(k_adam, grid1(m->n_params), dim3(256), 0, s, m->params, m->grads, m->adam_m,
@@ -1265,15 +1274,15 @@ static int prepare_infer(mgrhd_mlp* m, hipStream_t s, const float* x_mean, const
                                  96 * 1024) == hipSuccess;
   });
   if (!lds_ok) return MGRHD_E_DEVICE;
-  pack_weights(m, s);
+  pack_weights(m, m->infer, s);
   std::memset(&q, 0, sizeof(q));
   q.xmean = x_mean;
   q.xistd = x_istd;
   q.ymean = y_mean;
   q.ystd = y_std;
   for (int l = 0; l < 4; ++l) {
-    q.W[l] = m->wpack + m->wp_off[l];
-    q.b[l] = m->bpack + m->bp_off[l];
+    q.W[l] = m->infer.w + m->wp_off[l];
+    q.b[l] = m->infer.b + m->bp_off[l];
     q.K_pad[l] = m->k_pad[l];
     q.N_pad[l] = m->n_pad[l];
   }

@@ -400,3 +400,63 @@ def test_captured_training_step_follows_new_weights():
     torch.cuda.synchronize()
     assert np.array_equal(net.get_params(which=1), other.get_params(which=1))
     assert np.array_equal(net.get_params(), other.get_params())
+
+
+def _patch(ng, n):
+    edges = W.log_edges(1e-3, 1e3, ng)
+    dp, = synth.device_patches([W.PatchLayout(0, n, ng, 0, edges, edges[:-1] ** -2.0,
+                                              np.full(ng, -2.0))])
+    return dp
+
+
+def _warm(net, ng):
+    t = lambda x, k: torch.full((k,), x, dtype=torch.float32, device="cuda")
+    return warmstart.WarmStart(net, t(0.0, net.n_in), t(0.1, net.n_in), t(0.0, net.n_out),
+                               t(0.05, net.n_out), [])
+
+
+def test_training_leaves_the_inference_weights_alone():
+    """The copies of the weights that the fused inference reads change with an
+    inference, on its stream, and not with a training step, which may run on
+    another stream beside it: a captured inference gives the same guesses after
+    a training step, and the next eager one those of the new weights."""
+    ng = 4
+    net = _small_net(ng)
+    dp = _patch(ng, 300)
+    args = (dp.state, dp.tables, dp.kappa, dp.consts())
+    ws = _warm(net, ng)
+    first = ws.guess(*args, kind=0, fused=True)
+    graph, out = _graph_of(lambda: ws.guess(*args, kind=0, fused=True))
+    X, Y = _train_case(net, 64)
+    for _ in range(3):
+        net.train_step(X, Y, 1e-2)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, first)
+    now = ws.guess(*args, kind=0, fused=True)
+    other = _small_net(ng)
+    other.set_params(net.get_params())
+    assert torch.equal(now, _warm(other, ng).guess(*args, kind=0, fused=True))
+    assert not torch.equal(now, first)
+
+
+@pytest.mark.parametrize("ng,rows", [(1, 1), (1, 33), (4, 31), (16, 100), (15, 129), (31, 64),
+                                     (64, 4097), (138, 257), (4, 16417)])
+def test_weights_that_a_training_step_leaves(ng, rows):
+    """After a training step the next gradients, and the next inference, are
+    those of a network that was given the new weights: the copies that the step
+    writes are the new weights' at every width (every other path forms them
+    anew from the weights)."""
+    net = warmstart.MLP(2 + 3 * ng, 1 + ng, 128, max_rows=rows, seed=ng)
+    other = warmstart.MLP(2 + 3 * ng, 1 + ng, 128, max_rows=rows)
+    X, Y = _train_case(net, rows, seed=ng + rows)
+    for _ in range(2):
+        net.train_step(X, Y, 1e-2)
+    other.set_params(net.get_params())
+    loss = [float(n.gradients(X, Y).cpu()) for n in (net, other)]
+    assert loss[0] == loss[1]
+    assert np.array_equal(net.get_params(which=1), other.get_params(which=1))
+    dp = _patch(ng, 130)
+    args = (dp.state, dp.tables, dp.kappa, dp.consts())
+    a, b = (_warm(n, ng).guess(*args, kind=0, fused=True) for n in (net, other))
+    assert bool(torch.isfinite(a).all()) and torch.equal(a, b)
