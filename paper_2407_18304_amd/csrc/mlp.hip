@@ -434,9 +434,10 @@ __device__ __forceinline__ void tile_layer(const __bf16* in, int ldi, const __bf
   }
 }
 
-// sqrt(a) / b for b > 0 to two roundings: the hardware estimates refined by
-// Newton steps, without the range handling of the general square root and
-// division.  b below 1e-290 counts as that: the caller's a is then 0 (a square
+// sqrt(a) / b for b > 0 to two roundings: the hardware reciprocal square root
+// refined by a Goldschmidt step and two Newton corrections (as sqrt_1_4), times
+// a refined reciprocal, without the range handling of the general square root
+// and division.  b below 1e-290 counts as that: the caller's a is then 0 (a square
 // below the smallest number), or the quotient past its clamp at 2.
 __device__ __forceinline__ double sqrt_over(double a, double b) {
   const double y = __builtin_amdgcn_rsq(a);
@@ -766,7 +767,7 @@ struct mgrhd_mlp {
   struct Copies {
     __bf16* w = nullptr;   // [n_pad x k_pad] of every layer
     float* b = nullptr;    // [n_pad]
-    __bf16* wt = nullptr;  // transposes (training)
+    __bf16* wt = nullptr;  // transposes of layers 1 ... 3 (training)
     bool old = true;       // the weights have changed since
   };
   Copies infer, train;
@@ -883,7 +884,8 @@ static void pack_weights(mgrhd_mlp* m, mgrhd_mlp::Copies& c, hipStream_t s) {
     hipLaunchKernelGGL(k_pack, grid1((int64_t)m->n_pad[l] * m->k_pad[l]), dim3(256), 0, s,
                        m->params + m->w_off[l], m->params + m->b_off[l], m->out_dim[l],
                        m->in_dim[l], m->n_pad[l], m->k_pad[l], c.w + m->wp_off[l],
-                       c.b + m->bp_off[l], c.wt ? c.wt + m->wt_off[l] : nullptr, m->kt_pad[l]);
+                       c.b + m->bp_off[l], c.wt && l > 0 ? c.wt + m->wt_off[l] : nullptr,
+                       m->kt_pad[l]);
   c.old = capturing(s);
 }
 
@@ -915,7 +917,7 @@ static int train_pass(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld
   t.XT = take(m->k_pad[0]);
   for (int l = 0; l < 4; ++l) {
     t.W[l] = m->train.w + m->wp_off[l];
-    t.WT[l] = m->train.wt + m->wt_off[l];
+    if (l > 0) t.WT[l] = m->train.wt + m->wt_off[l];
     t.b[l] = m->train.b + m->bp_off[l];
     t.K_pad[l] = m->k_pad[l];
     t.N_pad[l] = m->n_pad[l];
@@ -979,7 +981,7 @@ static int train_pass(mgrhd_mlp* m, hipStream_t s, const float* X_fm, int64_t ld
     f.K_pad[l] = m->k_pad[l];
     f.kt_pad[l] = m->kt_pad[l];
     f.W[l] = m->train.w + m->wp_off[l];
-    f.WT[l] = m->train.wt + m->wt_off[l];
+    if (l > 0) f.WT[l] = m->train.wt + m->wt_off[l];
     f.b[l] = m->train.b + m->bp_off[l];
   }
   const unsigned blocks =
@@ -1056,7 +1058,7 @@ int mgrhd_mlp_create(int32_t n_in, int32_t n_hidden, int32_t n_out, int64_t max_
     btot += m->n_pad[l];
     m->kt_pad[l] = (dims[l + 1] + 31) / 32 * 32;
     m->wt_off[l] = ttot;
-    ttot += (int64_t)dims[l] * m->kt_pad[l];
+    if (l > 0) ttot += (int64_t)dims[l] * m->kt_pad[l];  // (no gradient of the inputs)
   }
   m->fused = n_hidden == kHT && m->k_pad[0] <= kMaxKin;
   // one allocation of what starts at zero (parameters, gradients, moments, the
