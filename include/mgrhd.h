@@ -284,16 +284,21 @@ int mgrhd_transport1d_stage(double* E_out, double* F_out, double* e_gas_out, dou
  * with its own n_cells), its own group count (1..128), edges and opacity
  * table; dt and c_hat are per patch, the options per batch.  All pointers are
  * DEVICE pointers owned by the caller and must stay valid while the batch is
- * used.  The patches are cut into work items of at most `chunk_cells` cells,
- * ordered by decreasing group count, and run by one workgroup each or taken
- * from a global counter (mgrhd_batch_set_item_scope; the counter is cleared by
- * a tiny kernel before the solver kernel, so the pair can be captured in a
- * hipGraph); each runs the per-cell solver of mgrhd_source_update with lanes
- * per cell = next power of two >= N_g / groups_per_lane.
- * A batch owns a small device work list and counter (allocated by
- * mgrhd_batch_create, freed by mgrhd_batch_destroy; the work list is rebuilt
- * by mgrhd_batch_set_tuning and mgrhd_batch_set_item_scope when the items
- * change, which must not overlap a run of the batch); mgrhd_batch_run, _capture and _launch
+ * used.  The patches are cut into work items, ordered by decreasing group
+ * count, and run by one workgroup each or taken from a global counter
+ * (mgrhd_batch_set_item_scope; the counter is cleared by a tiny kernel before
+ * the solver kernel, so the pair can be captured in a hipGraph); each runs the
+ * per-cell solver of mgrhd_source_update with lanes per cell = next power of
+ * two >= N_g / groups_per_lane.  An item from the counter holds at most
+ * chunk_cells cells; an item with a workgroup of its own holds as many rounds
+ * of the cells that the workgroup has in flight as half of the launch's rest
+ * gives each of them, at most chunk_cells cells where a cell takes 32 lanes (33
+ * to 64 groups) and as many times more or fewer where it takes fewer or more.
+ * A batch owns two small device work lists, one for either way, and a counter
+ * (allocated by mgrhd_batch_create, freed by mgrhd_batch_destroy; the lists are
+ * rebuilt by mgrhd_batch_set_tuning when the cells per item change, which must
+ * not overlap a run of the batch and ends the life of a caller's own graph of
+ * one; nothing else frees them); mgrhd_batch_run, _capture and _launch
  * allocate nothing.  Runs of one batch on several streams at once race on
  * that counter. */
 typedef struct {
@@ -344,16 +349,13 @@ int mgrhd_batch_set_tuning(mgrhd_batch* b, int32_t groups_per_lane, int32_t bloc
 int mgrhd_batch_get_tuning(const mgrhd_batch* b, int32_t* groups_per_lane,
                            int32_t* blocks_per_cu, int64_t* chunk_cells);
 /* Who takes a work item: 0 = one wave (each wave stages its patch's tables
- * in its own LDS slot); 1 or 2 = one workgroup (its four waves share the
- * item's cells through an LDS counter and one table slot).  Scope 1 at 2
- * groups per lane starts one workgroup per item, four per CU where every
- * patch's groups fill its lanes (N_g a power of two times 2) and three
- * otherwise; its items hold chunk_cells cells at most where a cell takes
- * 32 lanes (33 to 64 groups), as many more in narrower patches as run side by
- * side there, and fewer towards the end of the list.  Scope 2, and scope 1 at
- * 4 groups per lane, take items from a counter (2 waves per SIMD; waves that
- * run out of cells wait for the item's last cells).  Default 1.  Changing it
- * rebuilds the work list (as mgrhd_batch_set_tuning does) and drops a
+ * in its own LDS slot); 1 or 2 = one workgroup (its waves share the item's
+ * cells through an LDS counter and one table slot).  Scope 1 at 2 groups per
+ * lane starts one workgroup per item: eight waves, two workgroups per CU, where
+ * the patch's groups fill its lanes (N_g a power of two times 2), four waves
+ * and three per CU otherwise.  Scope 2, and scope 1 at 4 groups per lane, take
+ * items from a counter (four waves, 2 waves per SIMD; waves that run out of
+ * cells wait for the item's last cells).  Default 1.  Changing it drops a
  * captured graph.  get returns the scope or MGRHD_E_NULL. */
 int mgrhd_batch_set_item_scope(mgrhd_batch* b, int32_t per_workgroup);
 int32_t mgrhd_batch_get_item_scope(const mgrhd_batch* b);

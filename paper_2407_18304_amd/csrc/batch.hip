@@ -2,9 +2,9 @@
 // own cell count, group count, group edges and opacity table (the patch
 // layout of an adaptive mesh, where every patch holds its own SoA block).
 //
-// Work list: the patches are cut into items of at most `chunk` cells, ordered
-// by decreasing group count (the costliest work first, so the tail of the
-// launch is made of cheap items).  By default one workgroup runs one item and
+// Work lists: the patches are cut into items, ordered by decreasing group count
+// (the costliest work first, so the tail of the launch is made of cheap items;
+// batch_items.hpp).  By default one workgroup runs one item and
 // the hardware hands out the items (k_batch_items).  In the other scopes a wave
 // or a workgroup takes the next item with one atomic increment of a global
 // counter, stages that patch's tables in its LDS slot, sets its lane count per
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_wg(BatchArgs b) {
 // which leaves four waves per SIMD (k_source_update).  The patch's constants
 // are read where they are used (held in scalar registers they spilled 30 of
 // them in each state machine, 1% slower).  LDS is dynamic, as much as the
-// widest item of the launch needs.  Bound by the vector ALU as the
+// largest item of the launch needs.  Bound by the vector ALU as the
 // single-table kernel.  Taking items from a counter instead (k_batch_wg) asks
 // for an LDS slot for 128 groups, three workgroups per CU, and waits at every
 // item's end for the last of its cells: 24 patches of 1.3e6 cells 8.64 -> 8.04
@@ -248,13 +248,7 @@ __global__ __launch_bounds__((block_threads<G, FULL>()), FULL ? 4 : 3) void k_ba
     run_item_block<G, 64, MODE, FULL>(a, ap, item, batch_lds);
 }
 
-// Lanes per cell of N_g groups at 2 groups per lane, and the LDS of a
-// workgroup of k_batch_items with that many.
-static int item_lanes(int ng) {
-  int lpc = 1;
-  while (lpc * 2 < ng) lpc <<= 1;
-  return lpc;
-}
+// LDS of a workgroup of k_batch_items with lpc lanes per cell.
 template <bool FULL>
 static size_t item_lds(int lpc) {
   switch (lpc) {
@@ -310,23 +304,23 @@ struct mgrhd_batch {
   int64_t n_cells = 0;
   int32_t max_groups = 0;
   KArgs* d_patches = nullptr;
-  Item* d_items = nullptr;
   int32_t* d_counter = nullptr;
-  int64_t n_items = 0;
   std::vector<KArgs> h_patches;
   // tuning
   int32_t groups_per_lane = 2;
   int32_t scope = 1;          // 0: items per wave, 1 | 2: items per workgroup
   int32_t blocks_per_cu = 0;  // 0 = all resident
   int64_t chunk = 256;
+  // The two work lists, rebuilt when `chunk` changes and only then: a graph of
+  // the caller's that ran the batch reads the list of the scope it was captured
+  // in, whatever scope is set later.
   bool items_dirty = true;
-  // items of patches whose N_g fills its lanes at 2 groups per lane, the first
-  // of the work list; LDS of the widest such item and of the widest other
-  int64_t n_full = 0;
-  size_t lds_full = 0, lds_rest = 0;
-  // [first, last) item of each group count (the work list is sorted by
-  // decreasing N_g among the full and among the others), rebuilt with it
+  Item* d_items = nullptr;    // by cells (counter scopes, inference)
+  int64_t n_items = 0;
   std::vector<std::pair<int32_t, std::pair<int64_t, int64_t>>> ng_items;
+  Item* d_rounds = nullptr;   // by rounds (k_batch_items), the full ones first
+  int64_t n_rounds = 0, n_full = 0;
+  size_t lds_full = 0, lds_rest = 0;  // most LDS that a full item takes, and another
   // warm-start networks attached per group count (inference enqueued before
   // the solve)
   struct Net {
@@ -350,74 +344,34 @@ static int device_cus() {
   return cus;
 }
 
+static int upload_items(const std::vector<Item>& items, Item*& d) {
+  if (d) (void)hipFree(d);
+  d = nullptr;
+  if (items.empty()) return 0;
+  const size_t bytes = sizeof(Item) * items.size();
+  return hipMalloc(&d, bytes) == hipSuccess &&
+                 hipMemcpy(d, items.data(), bytes, hipMemcpyHostToDevice) == hipSuccess
+             ? 0 : MGRHD_E_DEVICE;
+}
+
 static int build_items(mgrhd_batch* bt) {
-  std::vector<Item> items;
-  std::vector<int32_t> order(bt->n_patches);
-  for (int32_t p = 0; p < bt->n_patches; ++p) order[p] = p;
-  auto full = [&](int32_t p) {
-    return 2 * item_lanes(bt->h_patches[p].ng) == bt->h_patches[p].ng;
-  };
-  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-    if (full(x) != full(y)) return full(x);
-    return bt->h_patches[x].ng > bt->h_patches[y].ng;
-  });
-  bt->ng_items.clear();
-  bt->n_full = 0;
-  bt->lds_full = bt->lds_rest = 0;
-  // With a workgroup per item (k_batch_items) the length of an item counts in
-  // rounds of the cells that a workgroup holds at once, not in cells: as many
-  // rounds for a narrow patch as for a wide one, and, as the hardware starts
-  // item after item, half of what the launch has left for each resident
-  // workgroup, so that all end together (block_range).  Measured: 24 patches
-  // of 1.3e6 cells 8.29 ms with 256 cells per item, 2.4 ms of it the last
-  // items of 64 groups.
-  const bool rounds = bt->scope == 1 && bt->groups_per_lane == 2;
-  constexpr int64_t kLeastRounds = 2;
-  auto in_flight = [](int32_t ng) {
-    const int lanes = item_lanes(ng);
-    return (int64_t)(item_threads(2 * lanes == ng) / lanes);
-  };
-  int64_t left[2] = {0, 0};  // rounds left of the full items and of the others
-  for (int32_t p : order) {
-    const KArgs& a = bt->h_patches[p];
-    left[full(p)] += (a.n + in_flight(a.ng) - 1) / in_flight(a.ng);
+  std::vector<PatchSize> sizes;
+  for (const KArgs& a : bt->h_patches) sizes.push_back(PatchSize{a.n, a.ng});
+  CellCut cells = cut_by_cells(sizes, bt->chunk);
+  const int threads[2] = {item_threads(false), item_threads(true)};
+  const RoundCut rounds = cut_by_rounds(sizes, bt->chunk, device_cus(), threads);
+  bt->n_items = (int64_t)cells.items.size();
+  bt->ng_items.swap(cells.ng_items);
+  bt->n_rounds = (int64_t)rounds.items.size();
+  bt->n_full = rounds.n_full;
+  // (few lanes per cell take room for many cells, many lanes for wide tables)
+  bt->lds_rest = bt->lds_full = 0;
+  for (int lanes = 1; lanes <= kWave; lanes *= 2) {
+    if (rounds.lanes[0] & lanes) bt->lds_rest = std::max(bt->lds_rest, item_lds<false>(lanes));
+    if (rounds.lanes[1] & lanes) bt->lds_full = std::max(bt->lds_full, item_lds<true>(lanes));
   }
-  // workgroups on the chip: four waves per SIMD of the full items, three of the others
-  auto resident = [](bool full) {
-    return (int64_t)device_cus() * (full ? 16 : 12) * kWave / item_threads(full);
-  };
-  const int64_t on_chip[2] = {resident(false), resident(true)};
-  for (int32_t p : order) {
-    const int64_t n = bt->h_patches[p].n;
-    const int32_t ng = bt->h_patches[p].ng;
-    if (bt->ng_items.empty() || bt->ng_items.back().first != ng)
-      bt->ng_items.push_back({ng, {(int64_t)items.size(), (int64_t)items.size()}});
-    for (int64_t c0 = 0; c0 < n;) {
-      int64_t cells = bt->chunk;
-      if (rounds) {
-        const int64_t r = std::max(left[full(p)] / (2 * on_chip[full(p)]), kLeastRounds);
-        cells = std::min(r * in_flight(ng),
-                         std::max<int64_t>(bt->chunk * 32 / item_lanes(ng), 1));
-        left[full(p)] -= (std::min(cells, n - c0) + in_flight(ng) - 1) / in_flight(ng);
-      }
-      const int64_t c1 = std::min(n, c0 + cells);
-      items.push_back(Item{p, 0, c0, c1});
-      c0 = c1;
-    }
-    bt->ng_items.back().second.second = (int64_t)items.size();
-    size_t& lds = full(p) ? bt->lds_full : bt->lds_rest;
-    lds = std::max(lds, full(p) ? item_lds<true>(item_lanes(ng)) : item_lds<false>(item_lanes(ng)));
-    if (full(p)) bt->n_full = (int64_t)items.size();
-  }
-  if (bt->d_items) (void)hipFree(bt->d_items);
-  bt->d_items = nullptr;
-  bt->n_items = (int64_t)items.size();
-  if (!items.empty()) {
-    if (hipMalloc(&bt->d_items, sizeof(Item) * items.size()) != hipSuccess) return MGRHD_E_DEVICE;
-    if (hipMemcpy(bt->d_items, items.data(), sizeof(Item) * items.size(), hipMemcpyHostToDevice) !=
-        hipSuccess)
-      return MGRHD_E_DEVICE;
-  }
+  if (const int rc = upload_items(cells.items, bt->d_items)) return rc;
+  if (const int rc = upload_items(rounds.items, bt->d_rounds)) return rc;
   bt->items_dirty = false;
   return 0;
 }
@@ -551,11 +505,10 @@ int mgrhd_batch_set_tuning(mgrhd_batch* bt, int32_t groups_per_lane, int32_t blo
   const bool changed = groups_per_lane != bt->groups_per_lane ||
                        blocks_per_cu != bt->blocks_per_cu || chunk_cells != bt->chunk;
   if (changed) drop_graph(bt);
-  const bool recut = chunk_cells != bt->chunk || groups_per_lane != bt->groups_per_lane;
   bt->groups_per_lane = groups_per_lane;
   bt->blocks_per_cu = blocks_per_cu;
-  if (recut) {
-    // the work list is rebuilt here, never inside run / capture / launch
+  if (chunk_cells != bt->chunk) {
+    // the work lists are rebuilt here, never inside run / capture / launch
     bt->chunk = chunk_cells;
     bt->items_dirty = true;
     return build_items(bt);
@@ -569,8 +522,6 @@ int mgrhd_batch_set_item_scope(mgrhd_batch* bt, int32_t per_workgroup) {
   if (per_workgroup != bt->scope) {
     bt->scope = per_workgroup;
     drop_graph(bt);
-    bt->items_dirty = true;
-    return build_items(bt);  // the items of scope 1 are cut by rounds
   }
   return 0;
 }
@@ -619,7 +570,7 @@ static int enqueue_items(const mgrhd_batch* bt, hipStream_t stream, bool full, i
                           (int)kCuLds) != hipSuccess)
     return MGRHD_E_DEVICE;
   hipLaunchKernelGGL(fn, dim3((unsigned)(hi - lo)), dim3(item_threads(full)), lds, stream,
-                     (const KArgs*)bt->d_patches, (const Item*)(bt->d_items + lo));
+                     (const KArgs*)bt->d_patches, (const Item*)(bt->d_rounds + lo));
   const hipError_t err = hipGetLastError();
   return err == hipSuccess ? 0 : (int)err;
 }
@@ -630,7 +581,7 @@ static int enqueue(mgrhd_batch* bt, hipStream_t stream) {
   if (const int rc = enqueue_infer(bt, stream)) return rc;
   if (bt->scope == 1 && bt->groups_per_lane == 2) {
     const int rc = enqueue_items(bt, stream, true, 0, bt->n_full);
-    return rc ? rc : enqueue_items(bt, stream, false, bt->n_full, bt->n_items);
+    return rc ? rc : enqueue_items(bt, stream, false, bt->n_full, bt->n_rounds);
   }
   BatchFn fn = batch_fn(bt->groups_per_lane, bt->mode, bt->scope);
   int nb = 0;
@@ -726,6 +677,7 @@ void mgrhd_batch_destroy(mgrhd_batch* bt) {
   drop_graph(bt);
   if (bt->d_patches) (void)hipFree(bt->d_patches);
   if (bt->d_items) (void)hipFree(bt->d_items);
+  if (bt->d_rounds) (void)hipFree(bt->d_rounds);
   if (bt->d_counter) (void)hipFree(bt->d_counter);
   delete bt;
 }
@@ -843,12 +795,10 @@ int mgrhd_batch_tune(mgrhd_batch* bt, mgrhd_stream_t stream) {
   for (const TuneCandidate& c : kTuneCandidates) {
     if (rc) break;
     if (bt->max_groups > c.groups_per_lane * 64) continue;
-    const bool recut = c.chunk != tmp.chunk || c.scope != tmp.scope ||
-                       c.groups_per_lane != tmp.groups_per_lane || tmp.items_dirty;
     tmp.groups_per_lane = c.groups_per_lane;
     tmp.scope = c.scope;
     tmp.blocks_per_cu = bt->blocks_per_cu;
-    if (recut) {
+    if (c.chunk != tmp.chunk || tmp.items_dirty) {
       tmp.chunk = c.chunk;
       if (hipStreamSynchronize(st) != hipSuccess) { rc = MGRHD_E_DEVICE; break; }
       if ((rc = build_items(&tmp)) != 0) break;
@@ -874,6 +824,7 @@ int mgrhd_batch_tune(mgrhd_batch* bt, mgrhd_stream_t stream) {
   (void)hipStreamSynchronize(st);
   if (tmp.d_patches) (void)hipFree(tmp.d_patches);
   if (tmp.d_items) (void)hipFree(tmp.d_items);
+  if (tmp.d_rounds) (void)hipFree(tmp.d_rounds);
   if (tmp.d_counter) (void)hipFree(tmp.d_counter);
   if (rc) return rc;
   if (!best) return MGRHD_E_OPTION;

@@ -7,18 +7,12 @@
 
 #include <cstdint>
 
+#include "batch_items.hpp"
 #include "solver_device.hpp"
 
 struct mgrhd_mlp;
 
 namespace mgrhd {
-
-// cells [c0, c1) of patch `patch`
-struct BatchItem {
-  int32_t patch;
-  int32_t pad;
-  int64_t c0, c1;
-};
 
 // 0 if the network m fits patches of n_groups groups (inputs 2 + 3 N_g,
 // outputs 1 + N_g, the fused path's hidden width), else MGRHD_E_SIZE.

@@ -453,3 +453,40 @@ def test_batch_out_of_place_needs_all_four_outputs():
     opt = mgrhd.default_options()
     assert L.mgrhd_batch_create(arr, 1, 1, C.byref(opt), C.byref(h)) == mgrhd.E_NULL
     assert not h.value
+
+
+@pytest.mark.parametrize("first,then", [((2, 1), [(2, 2), (4, 0), (4, 1)]),
+                                        ((2, 2), [(2, 1)]), ((4, 0), [(2, 1), (2, 0)])])
+def test_callers_graph_outlives_a_change_of_scope(first, then):
+    """A batch run captured in the caller's own graph stays whole when another
+    scope or number of groups per lane is set (both keep the cells per item,
+    hence the work lists that the graph reads)."""
+    layouts = _layouts(8)
+    dps = synth.device_patches(layouts)
+    pristine = [{k: v.clone() for k, v in dp.state.items()} for dp in dps]
+    b = mgrhd.Batch(_patch_dicts(dps), mean_mode=1, polish=1, **_consts())
+
+    def restore():
+        for dp, p in zip(dps, pristine):
+            for k in ("E_g", "F_g", "e_gas", "v"):
+                dp.state[k].copy_(p[k])
+
+    b.set_tuning(first[0], 0, 256)
+    b.set_item_scope(first[1])
+    b.run()
+    torch.cuda.synchronize()
+    ref = [{k: dp.state[k].clone() for k in ("E_g", "F_g", "e_gas", "v")} for dp in dps]
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(g, stream=s):
+        b.run(s.cuda_stream)
+    for gpl, scope in then:
+        b.set_tuning(gpl, 0, 256)
+        b.set_item_scope(scope)
+        restore()
+        b.run()
+        restore()
+        g.replay()
+        torch.cuda.synchronize()
+        for dp, r in zip(dps, ref):
+            for k in r:
+                assert torch.equal(dp.state[k], r[k]), (gpl, scope, k)
