@@ -91,7 +91,10 @@ inline RoundCut cut_by_rounds(const std::vector<PatchSize>& patches, int64_t chu
   for (int32_t p : order) {
     const int64_t n = patches[p].n, held = in_flight(p);
     const int lanes = item_lanes(patches[p].ng), f = full(p);
-    const int64_t most = std::max<int64_t>(chunk * 32 / lanes, 1);
+    // chunk * 32 / lanes, at least a cell, without overflow
+    const int64_t more = lanes < 32 ? 32 / lanes : 1, fewer = lanes > 32 ? lanes / 32 : 1;
+    const int64_t most =
+        chunk > INT64_MAX / more ? INT64_MAX : std::max<int64_t>(chunk * more / fewer, 1);
     for (int64_t c0 = 0, c1; c0 < n; c0 = c1) {
       const int64_t r = std::max(left[f] / (2 * on_chip[f]), kLeastRounds);
       const int64_t cells = std::min(std::min(r * held, most), n - c0);
