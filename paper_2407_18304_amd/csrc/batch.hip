@@ -569,10 +569,14 @@ static int enqueue_items(const mgrhd_batch* bt, hipStream_t stream, bool full, i
       hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)kCuLds) != hipSuccess)
     return MGRHD_E_DEVICE;
-  hipLaunchKernelGGL(fn, dim3((unsigned)(hi - lo)), dim3(item_threads(full)), lds, stream,
-                     (const KArgs*)bt->d_patches, (const Item*)(bt->d_rounds + lo));
-  const hipError_t err = hipGetLastError();
-  return err == hipSuccess ? 0 : (int)err;
+  // a launch holds fewer than 2^32 threads: 8.4e6 items of 512
+  const int64_t most = (int64_t)UINT32_MAX / item_threads(full);
+  for (; lo < hi; lo += most) {
+    hipLaunchKernelGGL(fn, dim3((unsigned)std::min(most, hi - lo)), dim3(item_threads(full)), lds,
+                       stream, (const KArgs*)bt->d_patches, (const Item*)(bt->d_rounds + lo));
+    if (const hipError_t err = hipGetLastError()) return (int)err;
+  }
+  return 0;
 }
 
 static int enqueue(mgrhd_batch* bt, hipStream_t stream) {

@@ -490,3 +490,35 @@ def test_callers_graph_outlives_a_change_of_scope(first, then):
         for dp, r in zip(dps, ref):
             for k in r:
                 assert torch.equal(dp.state[k], r[k]), (gpl, scope, k)
+
+
+def test_more_items_than_one_launch_holds():
+    """One cell per item over more cells than workgroups of 512 threads fit a
+    launch (2^32 threads).  The cells at both ends and around the limit of one
+    launch are updated as alone; the others hold no matter and are refused."""
+    limit, ng = (2 ** 32 - 1) // 512, 64
+    n = limit + 300
+    edges = W.log_edges(1e-3, 1e3, ng)
+    lay = W.PatchLayout(0, 400, ng, 0, edges, edges[:-1] ** -2.0, np.full(ng, -2.0))
+    dp, = synth.device_patches([lay])
+    at = torch.cat([torch.arange(100), torch.arange(limit - 100, limit + 100),
+                    torch.arange(n - 100, n)]).cuda()
+    pick = lambda v, shape: torch.zeros(shape + (n,), dtype=torch.float64,
+                                        device="cuda").index_copy_(-1, at, v)
+    big = {k: pick(v, tuple(v.shape[:-1])) for k, v in dp.state.items()}
+    status = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    p, = _patch_dicts([dp])
+    p["trace"] = None
+    small = dict(p, **{k: v.clone() for k, v in dp.state.items()})
+    p.update(big, kappa_scale=pick(dp.kappa, ()), status=status, iters=None, outer=None)
+    for d in (small, p):
+        b = mgrhd.Batch([d], mean_mode=1, polish=1, **_consts())
+        b.set_tuning(2, 0, 1)
+        b.run()
+        torch.cuda.synchronize()
+        b.close()
+    for k in ("E_g", "F_g", "e_gas", "v"):
+        assert torch.equal(big[k][..., at], small[k]), k
+    assert torch.equal(status[at], small["status"])
+    status[at] = mgrhd.ST_INVALID
+    assert bool((status == mgrhd.ST_INVALID).all())
