@@ -219,11 +219,13 @@ __global__ __launch_bounds__(kBlock, 2) void k_batch_wg(BatchArgs b) {
 template <int G, int LPC, int MODE, bool FULL>
 __device__ __forceinline__ void run_item_block(const KArgs& a, KArgsRef ap, const Item& item,
                                                unsigned char* lds) {
-  run_block<G, LPC, MODE, false, FULL>(a, ap, item.c0, item.c1, *(BlockLds<G, LPC, FULL, true>*)lds);
+  constexpr int kThreads = block_threads<G, FULL, MODE, false>();
+  run_block<G, LPC, MODE, false, FULL>(a, ap, item.c0, item.c1,
+                                       *(BlockLds<G, LPC, kThreads, true>*)lds);
 }
 
 template <int G, int MODE, bool FULL>
-__global__ __launch_bounds__((block_threads<G, FULL>()), FULL ? 4 : 3) void k_batch_items(
+__global__ __launch_bounds__((block_threads<G, FULL, MODE, false>()), FULL ? 4 : 3) void k_batch_items(
     const KArgs* patches, const Item* items) {
   extern __shared__ __attribute__((aligned(16))) unsigned char batch_lds[];
   typedef const Item __attribute__((address_space(4)))* ItemRef;
@@ -248,22 +250,23 @@ __global__ __launch_bounds__((block_threads<G, FULL>()), FULL ? 4 : 3) void k_ba
     run_item_block<G, 64, MODE, FULL>(a, ap, item, batch_lds);
 }
 
-// LDS of a workgroup of k_batch_items with lpc lanes per cell.
+// Threads of a workgroup of k_batch_items (of any mean mode), and its LDS with
+// lpc lanes per cell.
+template <bool FULL>
+constexpr int kItemThreads = block_threads<2, FULL, MGRHD_MEAN_PPL_FREE, false>();
 template <bool FULL>
 static size_t item_lds(int lpc) {
   switch (lpc) {
-    case 1: return sizeof(BlockLds<2, 1, FULL>);
-    case 2: return sizeof(BlockLds<2, 2, FULL>);
-    case 4: return sizeof(BlockLds<2, 4, FULL>);
-    case 8: return sizeof(BlockLds<2, 8, FULL>);
-    case 16: return sizeof(BlockLds<2, 16, FULL>);
-    case 32: return sizeof(BlockLds<2, 32, FULL>);
-    default: return sizeof(BlockLds<2, 64, FULL>);
+    case 1: return sizeof(BlockLds<2, 1, kItemThreads<FULL>>);
+    case 2: return sizeof(BlockLds<2, 2, kItemThreads<FULL>>);
+    case 4: return sizeof(BlockLds<2, 4, kItemThreads<FULL>>);
+    case 8: return sizeof(BlockLds<2, 8, kItemThreads<FULL>>);
+    case 16: return sizeof(BlockLds<2, 16, kItemThreads<FULL>>);
+    case 32: return sizeof(BlockLds<2, 32, kItemThreads<FULL>>);
+    default: return sizeof(BlockLds<2, 64, kItemThreads<FULL>>);
   }
 }
-static int item_threads(bool full) {
-  return full ? block_threads<2, true>() : block_threads<2, false>();
-}
+static int item_threads(bool full) { return full ? kItemThreads<true> : kItemThreads<false>; }
 
 using ItemsFn = void (*)(const KArgs*, const Item*);
 static ItemsFn items_fn(int mode, bool full) {

@@ -180,9 +180,13 @@ constexpr int kBlock = 256;
 // per CU then waits for its last cell).  The others hold three waves per SIMD,
 // of which 512 threads would leave one empty, or are small launches, which 512
 // threads would leave on half of the CUs.
-template <int G, bool FULL>
+template <int G, bool FULL, int MODE, bool TD>
+constexpr bool four_waves() {
+  return FULL && G == 2 && !(TD && MODE == MGRHD_MEAN_PPL_FREE);
+}
+template <int G, bool FULL, int MODE, bool TD>
 constexpr int block_threads() {
-  return FULL && G == 2 ? 512 : kBlock;
+  return four_waves<G, FULL, MODE, TD>() ? 512 : kBlock;
 }
 constexpr int kWave = 64;
 constexpr double kThird = 1.0 / 3.0;

@@ -13,9 +13,9 @@ namespace mgrhd {
 // LDS of one workgroup of the state machine with LPC lanes per cell: the group
 // tables, the per-lane slots, the per-cell area, and the cells of the
 // workgroup's range handed out so far.  AT_USE: LaneStore's CONST_AT_USE.
-template <int G, int LPC, bool FULL, bool AT_USE = false>
+template <int G, int LPC, int THREADS, bool AT_USE = false>
 struct BlockLds {
-  static constexpr int kThreads = block_threads<G, FULL>();
+  static constexpr int kThreads = THREADS;
   using LS = LaneStore<G, true, kThreads / LPC, AT_USE, kThreads>;
   Tables<G * LPC> tab;
   double lane[LS::kSlots * kThreads];
@@ -26,11 +26,11 @@ struct BlockLds {
 // The cells [lo, hi) of one state by this workgroup: its tables staged, the
 // cells shared by its waves through the counter in LDS.  ap: the argument
 // block that a was read from.
-template <int G, int LPC, int MODE, bool TD, bool FULL, bool AT_USE>
+template <int G, int LPC, int MODE, bool TD, bool FULL, int THREADS, bool AT_USE>
 __device__ __forceinline__ void run_block(const KArgs& a, KArgsRef ap, int64_t lo, int64_t hi,
-                                          BlockLds<G, LPC, FULL, AT_USE>& lds) {
+                                          BlockLds<G, LPC, THREADS, AT_USE>& lds) {
   constexpr int NGM = G * LPC;
-  using LS = typename BlockLds<G, LPC, FULL, AT_USE>::LS;
+  using LS = typename BlockLds<G, LPC, THREADS, AT_USE>::LS;
   const LS ls{lds.lane + threadIdx.x, lds.cell, ap};
   if (threadIdx.x == 0) lds.taken = 0;
   const bool table_ok = stage_tables<NGM, MODE>(a, lds.tab);  // (its barriers publish `taken`)
@@ -57,11 +57,20 @@ __device__ __forceinline__ void run_block(const KArgs& a, KArgsRef ap, int64_t l
 // Without the per-slot checks the FULL kernels of two groups per lane fit the
 // 128 registers of four waves per SIMD, whatever the variant asks for (2^21
 // cells x 16 groups 4.35 -> 4.00 ms, PPL-free 5% faster; with the checks they
-// would spill: 11 groups 1.19 -> 1.47 ms).
+// would spill: 11 groups 1.19 -> 1.47 ms).  PPL-free with a temperature-dependent
+// opacity does not: at four waves it spills, and at 64 groups the compiler then
+// puts copies of split registers before the end of a branch's lanes, so that the
+// other lanes go on with stale ones.  It keeps three waves.
+template <int G, int MODE, int WPE, bool TD, bool FULL>
+constexpr int waves_per_simd() {
+  if (four_waves<G, FULL, MODE, TD>()) return WPE < 4 ? 4 : WPE;
+  return FULL && G == 2 && WPE > 3 ? 3 : WPE;
+}
 template <int G, int LPC, int MODE, int WPE, bool TD, bool FULL>
-__global__ __launch_bounds__((block_threads<G, FULL>()), FULL && G == 2 && WPE < 4 ? 4 : WPE) void
+__global__ __launch_bounds__((block_threads<G, FULL, MODE, TD>()),
+                             (waves_per_simd<G, MODE, WPE, TD, FULL>())) void
 k_source_update(KArgs a) {
-  __shared__ BlockLds<G, LPC, FULL> lds;
+  __shared__ BlockLds<G, LPC, block_threads<G, FULL, MODE, TD>()> lds;
   // the arguments as the device reads them in place (a is the only argument)
   const KArgsRef ap = (KArgsRef)__builtin_amdgcn_kernarg_segment_ptr();
   // each workgroup owns a contiguous range of cells, shared by its waves

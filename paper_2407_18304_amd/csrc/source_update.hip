@@ -102,16 +102,21 @@ static Variant* choose_variant(int ng) {
   return find_variant(lpc, 4, 0);
 }
 
-// resident workgroups per CU of a variant (queried once)
-static int variant_threads(const Variant* v, int full) {
-  return full && v->g == 2 ? block_threads<2, true>() : kBlock;
+// threads of a workgroup of a variant
+static int variant_threads(const Variant* v, int td, int full, int mode) {
+  if (!full || v->g != 2) return kBlock;
+  return td && mode == MGRHD_MEAN_PPL_FREE
+             ? block_threads<2, true, MGRHD_MEAN_PPL_FREE, true>()
+             : block_threads<2, true, MGRHD_MEAN_PPL_FREE, false>();
 }
+
+// resident workgroups per CU of a variant (queried once)
 static int resident_blocks(Variant* v, int td, int full, int mode) {
   std::lock_guard<std::mutex> lk(g_mutex);
   int& nb = v->blocks_per_cu[td][full][mode];
   if (nb == 0) {
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, v->fn[td][full][mode],
-                                                     variant_threads(v, full), 0) !=
+                                                     variant_threads(v, td, full, mode), 0) !=
             hipSuccess ||
         nb < 1)
       nb = 1;
@@ -349,7 +354,7 @@ int mgrhd_source_update(double* E_g, double* F_g, const double* rho, double* e_g
   const int full = var->lpc * var->g == ng ? 1 : 0;  // every slot holds a group
   const int64_t resident =
       (int64_t)num_cus() * resident_blocks(var, td, full, op->mean_mode);
-  const int threads = variant_threads(var, full);
+  const int threads = variant_threads(var, td, full, op->mean_mode);
   const int64_t blocks = plan_blocks(a, threads / var->lpc, resident);
   hipLaunchKernelGGL(var->fn[td][full][op->mean_mode], dim3((unsigned)blocks), dim3(threads), 0,
                      (hipStream_t)stream, a);

@@ -105,3 +105,23 @@ def test_temperature_argument_errors():
     assert (gs == mgrhd.ST_BAD_TABLE).all()
     for k in U.FIELDS:
         assert np.array_equal(g[k], w.state[k])
+
+
+# every split of two groups per lane that the groups fill, the largest of them
+# the one that holds the most registers
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("ng,waves", [(4, 0), (8, 0), (16, 0), (16, 4), (32, 0), (64, 0), (64, 4)])
+def test_groups_that_fill_two_per_lane(ng, waves, mode):
+    """(T/T_ref)^(-1/2) with the stimulated-emission factor: parity with the
+    oracle, and the same bits in a second run."""
+    w = W.config1(cells=np.arange(1500), ng=ng)
+    w.t_exp, w.t_ref, w.stim = -0.5, 0.8, 1
+    try:
+        mgrhd.set_variant(ng, ng // 2, 2, waves)
+        first = U.run_gpu(w, mode)
+        again = U.run_gpu(w, mode)
+    finally:
+        mgrhd.set_variant(ng, 0, 0)
+    U.compare(w, first, U.run_oracle(w, mode), label=f"{ng} groups, mode {mode}")
+    for k, v in first[0].items():
+        assert np.array_equal(v, again[0][k]), k
