@@ -186,7 +186,9 @@ int mgrhd_source_update(double* E_g, double* F_g, const double* rho, double* e_g
 
 /* Kernel variant used for a given group count (launches too small to fill the
  * GPU, and most PPL-free ones, may split a cell over one lane per group unless
- * mgrhd_set_variant has been called for that count): lanes per cell, groups per
+ * mgrhd_set_variant has been called for that count, with the same results bit
+ * for bit: a cell's do not depend on how many cells a launch has): lanes per
+ * cell, groups per
  * lane and the register budget, given as the minimum resident waves per SIMD
  * it is compiled for (more waves: fewer registers per lane).
  * mgrhd_set_variant overrides the built-in choice for n_groups (0, 0, 0

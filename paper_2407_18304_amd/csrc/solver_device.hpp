@@ -251,10 +251,36 @@ __device__ __forceinline__ double butterfly(double v) {
   return row_swap_sum<M>(v);
 }
 
+// a + b, kept out of a fused multiply-add with a product that b may be: the
+// sums over a cell's groups add the rounded terms, so that they do not depend
+// on which of the terms a lane adds up by itself.
+__device__ __forceinline__ double plus(double a, double b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+
+// v + the value of the lane at distance n/2 of a cell group of n lanes
+// (a distance that adds and subtracts alike), nothing summed before.
+template <int N>
+__device__ __forceinline__ double half_swap_sum(double v) {
+  if (N <= 4) return butterfly<N / 2>(v);
+  if (N == 8) return v + dpp_swap<0x1B>(dpp_swap<0x141>(v));  // mirrored half row, mirrored quads
+  if (N == 16) return v + dpp_swap<0x128>(v);                 // row_ror:8
+  return row_swap_sum<N / 2>(v);
+}
+
 // Sum over the lanes of one cell group (bit-identical in every lane).  LPC = 0:
-// the group size lpc is a run-time value, uniform over the wave.
-template <int LPC>
+// the group size lpc is a run-time value, uniform over the wave.  With one
+// group per lane (G = 1) lanes j and j + LPC/2 hold what slots 0 and 1 of lane j
+// hold with two, and their sum is taken first, as a lane of two takes it: the
+// same sum bit for bit, so a cell's result does not depend on how many cells a
+// launch has (launch_variant).
+template <int G, int LPC>
 __device__ __forceinline__ double cell_sum(double v, int lpc) {
+  if constexpr (G == 1 && LPC >= 2) {
+    v = half_swap_sum<LPC>(v);
+    return cell_sum<2, LPC / 2>(v, LPC / 2);
+  }
   const int n = LPC > 0 ? LPC : lpc;
   if (n >= 2) v = butterfly<1>(v);
   if (n >= 4) v = butterfly<2>(v);
@@ -725,7 +751,7 @@ __device__ __forceinline__ void load_cell(const KArgs& a, const Tables<NGM>& t, 
       const double sg = S ? S[(int64_t)g * n + i] : 0.0;
       ok = ok && e >= 0.0 && isfinite(e) && isfinite(sg);
       s.E0[k] = e + sg;
-      sumE += e + sg;
+      sumE = plus(sumE, e + sg);
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         f[d] = sp.F[((int64_t)d * ng + g) * n + i];
@@ -747,8 +773,8 @@ __device__ __forceinline__ void load_cell(const KArgs& a, const Tables<NGM>& t, 
       ls.iJgg(k) = ij;
     }
   }
-  sumE = cell_sum<LPC>(sumE, s.lpc);
-  const double bad = cell_sum<LPC>(ok ? 0.0 : 1.0, s.lpc);
+  sumE = cell_sum<G, LPC>(sumE, s.lpc);
+  const double bad = cell_sum<G, LPC>(ok ? 0.0 : 1.0, s.lpc);
   s.ke = 0.5 * s.rho * (s.v[0] * s.v[0] + s.v[1] * s.v[1] + s.v[2] * s.v[2]);
   s.etot = s.egas0 + ls.cst(a, &KArgs::icc) * sumE;  // E_tot of Sec. 3
   ok = bad == 0.0 && (s.egas0 - s.ke) > 0.0 && s.etot > 0.0;
@@ -792,7 +818,7 @@ __device__ __forceinline__ void finish_cell(const KArgs& a, int j, CellState<G>&
       for (int d = 0; d < 3; ++d)
         if (!isfinite(ls.F(d, k))) bad = 1.0;
     }
-    bad = cell_sum<LPC>(bad, s.lpc);
+    bad = cell_sum<G, LPC>(bad, s.lpc);
     const StatePtrs p = state_ptrs(ls.args);
     if (bad != 0.0) {
       s.st |= MGRHD_ST_NONFINITE;
@@ -855,8 +881,8 @@ __device__ __forceinline__ void newton_done(const KArgs& a, int j, CellState<G>&
   // conservative energy update (Sec. 3)
   double sumR = 0.0;
 #pragma unroll
-  for (int k = 0; k < G; ++k) sumR += s.R[k];
-  sumR = cell_sum<LPC>(sumR, s.lpc);
+  for (int k = 0; k < G; ++k) sumR = plus(sumR, s.R[k]);
+  sumR = cell_sum<G, LPC>(sumR, s.lpc);
   s.egv = s.egas0 - ls.cst(a, &KArgs::cc) * sumR;  // E_gas^(t+1) of this pass
   s.phase = P_FLUX;
 }
@@ -925,15 +951,15 @@ __device__ __forceinline__ void newton_step(const KArgs& a, const Tables<NGM>& t
     const double Jg0 = ratio * c.dBdT[k] * ircv;               // eq. linear
     ag[k] = FR * iJgg;
     bg[k] = Jg0 * iJgg;
-    sumR += s.R[k];
-    sumAbs += fabs(FR);
-    sumA += ag[k];
-    sumB += bg[k];
+    sumR = plus(sumR, s.R[k]);
+    sumAbs = plus(sumAbs, fabs(FR));
+    sumA = plus(sumA, ag[k]);
+    sumB = plus(sumB, bg[k]);
   }
-  sumR = cell_sum<LPC>(sumR, s.lpc);
-  sumAbs = cell_sum<LPC>(sumAbs, s.lpc);
-  sumA = cell_sum<LPC>(sumA, s.lpc);
-  sumB = cell_sum<LPC>(sumB, s.lpc);
+  sumR = cell_sum<G, LPC>(sumR, s.lpc);
+  sumAbs = cell_sum<G, LPC>(sumAbs, s.lpc);
+  sumA = cell_sum<G, LPC>(sumA, s.lpc);
+  sumB = cell_sum<G, LPC>(sumB, s.lpc);
   const double FG = s.egv - s.egas0 + cc * sumR;
   // the stop test of Sec. 3, |F_G| / E_tot < eps and (c/c_hat) sum |F_R,g| / E_tot < eps
   const double tol = ls.cst(a, &KArgs::eps) * s.etot;
@@ -1004,7 +1030,7 @@ __device__ __forceinline__ bool flux_step(const KArgs& a, const Tables<NGM>& t, 
       const double f0 = LS::kKeep0 ? ls.F0(d, k) : a.F[((int64_t)d * ng + g) * n + i];  // F_g^(t)
       const double f = (f0 + cdt * (s.v[d] * c.emit[k] + q * Pv[d])) * iden;
       ls.F(d, k) = f;  // F_k+1 replaces F_k (v_k . F_k stays in s.vF)
-      dmom[d] += f - f0;
+      dmom[d] = plus(dmom[d], f - f0);
     }
   }
   const double ccc = ls.cst(a, &KArgs::iccc);
@@ -1012,7 +1038,7 @@ __device__ __forceinline__ bool flux_step(const KArgs& a, const Tables<NGM>& t, 
   double vn[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    dmom[d] = cell_sum<LPC>(dmom[d], s.lpc);
+    dmom[d] = cell_sum<G, LPC>(dmom[d], s.lpc);
     const double v0 = LS::kKeep0 ? ls.v0(d) : a.v[(int64_t)d * n + i];  // v^(t)
     vn[d] = (s.rho * v0 - dmom[d] * ccc) * irho;  // momentum update
   }
@@ -1026,10 +1052,10 @@ __device__ __forceinline__ bool flux_step(const KArgs& a, const Tables<NGM>& t, 
     if (g >= ng) continue;
     const double vf_new = vn[0] * ls.F(0, k) + vn[1] * ls.F(1, k) + vn[2] * ls.F(2, k);
     const double kw = fabs((1.0 + (TD ? c.ac[k] : t.achi[g])) * c.chiF[k]);
-    dW += kw * fma(-0x1p-46, fabs(vf_new), fabs(vf_new - s.vF[k]));
+    dW = plus(dW, kw * fma(-0x1p-46, fabs(vf_new), fabs(vf_new - s.vF[k])));
     s.vF[k] = vf_new;
   }
-  dW = cell_sum<LPC>(dW, s.lpc) * ls.cst(a, &KArgs::cdt_ic2);
+  dW = cell_sum<G, LPC>(dW, s.lpc) * ls.cst(a, &KArgs::cdt_ic2);
   const double ke_new = 0.5 * s.rho * (vn[0] * vn[0] + vn[1] * vn[1] + vn[2] * vn[2]);
   const double egas_new = s.egv;
   s.egv = egas_new + (ke_new - s.ke);

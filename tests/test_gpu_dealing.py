@@ -120,3 +120,64 @@ def test_split_of_a_small_launch(ng, split, n, mode):
     assert torch.equal(st, want_st)
     for k in KEYS:
         _close(got[k], want[k], (ng, n, k))
+
+
+def _all(state, tables, kappa, consts, mode):
+    """Every output of an update of this state."""
+    n = kappa.numel()
+    out = tuple(torch.empty_like(state[k]) for k in KEYS)
+    counts = {k: torch.full((n,), -7, dtype=torch.int32, device="cuda")
+              for k in ("iters", "outer", "status")}
+    mgrhd.source_update(state["E_g"], state["F_g"], state["rho"], state["e_gas"], state["v"],
+                        tables["edges"], tables["chi_lo"], alpha_chi=tables["alpha"],
+                        kappa_scale=kappa, polish=1, out=out, mean_mode=mode, **counts, **consts)
+    return dict(zip(KEYS, out), **counts)
+
+
+def _cells(ng, n, td):
+    edges = W.log_edges(1e-3, 1e3, ng)
+    dp, = synth.device_patches([W.PatchLayout(0, n, ng, 0, edges, edges[:-1] ** -2.0,
+                                              torch.full((ng,), -2.0).double().numpy())])
+    more = dict(t_exp=-0.5, t_ref=0.8, stim=1) if td else {}
+    return dp.state, dp.tables, dp.kappa, dict(dp.consts(), **more)
+
+
+# groups that fill the lanes of both splits and that do not, every lane count
+# of one group per lane (4 to 64)
+@pytest.mark.parametrize("td", [False, True])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("ng", [1, 2, 3, 4, 5, 8, 11, 16, 17, 32, 33, 64])
+def test_both_splits_give_the_same_bits(ng, mode, td):
+    """One group per lane and the split that larger launches take: every
+    output of every cell equal bit for bit."""
+    args = _cells(ng, 4096, td)
+    one = 4
+    while one < ng:
+        one *= 2
+    many = (1, 4) if ng <= 2 else (one // 2, 2)
+    got = []
+    try:
+        for lanes, groups in ((one, 1), many):
+            mgrhd.set_variant(ng, lanes, groups)
+            got.append(_all(*args, mode))
+    finally:
+        mgrhd.set_variant(ng, 0, 0)
+    for k in got[0]:
+        assert torch.equal(got[0][k], got[1][k]), (k, int((got[0][k] != got[1][k]).sum()))
+
+
+@pytest.mark.parametrize("ng,n,mode,td", [(4, 131072, 1, False), (16, 32768, 0, False),
+                                          (64, 16384, 2, False), (11, 40000, 1, False),
+                                          (16, 24576, 1, True)])
+def test_a_grid_in_pieces_gives_its_bits(ng, n, mode, td):
+    """A grid whose launch takes two groups per lane, and the same cells in
+    launches small enough for one."""
+    state, tables, kappa, consts = _cells(ng, n, td)
+    whole = _all(state, tables, kappa, consts, mode)
+    step = n // 16 + 3
+    for i in range(0, n, step):
+        at = slice(i, min(n, i + step))
+        part = {k: v[..., at].contiguous() for k, v in state.items()}
+        got = _all(part, tables, kappa[at].contiguous(), consts, mode)
+        for k in got:
+            assert torch.equal(got[k], whole[k][..., at]), (k, i)
