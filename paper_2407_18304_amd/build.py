@@ -2,6 +2,7 @@
 
     libmgrhd.so        the source-update kernels and the C ABI of include/mgrhd.h
     libmgrhd_synth.so  the seeded synthetic-input generator (test/bench inputs)
+    libmgrhd_probe.so  the kernels' inner functions element by element (tests)
 """
 from __future__ import annotations
 
@@ -29,6 +30,7 @@ LIBS = {
                     "source_update_tdep_full.hip", "batch.hip", "mlp.hip", "imex.hip",
                     "transport1d.hip"],
     "libmgrhd_synth.so": ["synth.hip"],
+    "libmgrhd_probe.so": ["math_probe.hip"],
 }
 
 

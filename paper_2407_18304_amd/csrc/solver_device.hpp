@@ -350,8 +350,7 @@ __device__ __forceinline__ bool table_group(const KArgs& a, Tables<NGM>& t, int 
     mf = mean_ratio(ac, -1.0, L);
     rac = exp(ac * L);
     ldn = log(hi - lo);
-    if (MODE == MGRHD_MEAN_PPL_FREE && g > 0)
-      rdl = 1.0 / (0.5 * (log(lo) + log(hi)) - 0.5 * (log(t.nu[g - 1]) + log(lo)));
+    if (MODE == MGRHD_MEAN_PPL_FREE && g > 0) rdl = 2.0 / (L + log(lo / t.nu[g - 1]));
   }
   t.lnr[g] = L;
   t.achi[g] = ac;
@@ -565,10 +564,10 @@ __device__ __forceinline__ void evaluate(const Tables<NGM>& t, int ng, int j, in
         } else {
           double ac = t.achi[g], rac = t.rac[g], mr = t.mfix[g];
           if (ot.stim) {
-            const double q = s_hi * rcp_nr(s_lo);
+            const double q = div_nr(s_hi, s_lo);
             const double lq = log_pos(q);
             mr = mean_fixed_rac(fma(ac, t.lnr[g], lq), rac * q);  // eq. chiQg, alpha_Q = -1
-            ac = fma(lq, rcp_nr(t.lnr[g]), ac);
+            ac += div_nr(lq, t.lnr[g]);
             rac *= q;
           }
           const double ch = chl * mr;
@@ -597,7 +596,7 @@ __device__ __forceinline__ void evaluate(const Tables<NGM>& t, int ng, int j, in
         const double s_hi = stim_factor(hi);
         slo[k] = from_left<LPC>(last ? prev_s : s_hi, lpc);
         prev_s = s_hi;
-        sq[k] = s_hi * rcp_nr(slo[k]);
+        sq[k] = div_nr(s_hi, slo[k]);
       }
       lqB[k] = -INFINITY;
       lqE[k] = -INFINITY;
@@ -624,7 +623,7 @@ __device__ __forceinline__ void evaluate(const Tables<NGM>& t, int ng, int j, in
       if (TD) {
         chl *= ot.fT * slo[k];
         if (ot.stim) {
-          ac = fma(log_pos(sq[k]), rcp_nr(L), ac);
+          ac += div_nr(log_pos(sq[k]), L);
           rac *= sq[k];
         }
         c.ac[k] = ac;

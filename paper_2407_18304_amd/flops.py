@@ -41,7 +41,7 @@ CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")
 
 # FLOP-equivalents of one call on gfx950 (measured by measure_weights())
 W = {"exp": 29, "expm1": 34, "log": 84, "div": 17, "sqrt": 19, "exp_neg": 34, "rcp_nr": 9,
-     "sqrt_1_4": 17, "div_nr": 14, "log_pos": 42, "one_minus_exp": 38}
+     "sqrt_1_4": 17, "div_nr": 14, "log_pos": 50, "one_minus_exp": 38}
 
 PC, FIXED, FREE = 0, 1, 2
 
@@ -110,10 +110,10 @@ def unit_costs(w=W):
     # 1/J_gg (no longer per-cell constants); the cell load skips them.
     td = dict(
         ev_cell_pow=1 + lp + e + 1,
-        edge_stim={"nonwien": 2 + rc, "wien": 1},
+        edge_stim={"nonwien": 1 + dn, "wien": 1},
         ev_group={PC: 2, FIXED: 3, FREE: 2},
-        ev_group_stim={PC: 1, FIXED: 1 + (1 + rc) + lp + (2 + rc) + 1 + 2 + (om + rc + 3),
-                       FREE: 1 + (1 + rc) + lp + (2 + rc) + 1},
+        ev_group_stim={PC: 1, FIXED: 1 + dn + lp + (1 + dn) + 1 + 2 + (om + rc + 3),
+                       FREE: 1 + dn + lp + (1 + dn) + 1},
         nt_group={PC: 2 * (1 + rc), FIXED: 2 * (1 + rc), FREE: 0},
         ld_group={PC: -((2 + dv) + (1 + rc)), FIXED: -((2 + dv) + (1 + rc)), FREE: 0},
     )

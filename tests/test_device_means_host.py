@@ -100,3 +100,15 @@ def test_means_of_the_inner_loop(dm, L):
         y = abs(ac) * L
         got = dm.dm_mean_fixed_rac(ac * L, rac)
         assert abs(got - fixed) <= (16 + 4 * y) * U * fixed, ac
+
+
+def test_log_pos_rounding(dm):
+    """Within 2 U: the rounding of the result, a fifth of one of the corrected
+    f (its share of the logarithm), and a fifth of the some 2.8 of s and of the
+    series; the parts that e ln2 loses are added again."""
+    rng = np.random.default_rng(5)
+    xs = np.concatenate([[1.0, 0.5, 2.0, 0.7071067811865475, 0.7071067811865476, 5e-324, 1.7e308],
+                         rng.uniform(0.5, 2.0, 4000), 10.0 ** rng.uniform(-320, 308, 4000)])
+    for x in xs:
+        ref = mp.log(mp.mpf(float(x)))
+        assert abs(dm.dm_log_pos(float(x)) - ref) <= 2 * U * abs(ref), x
