@@ -359,7 +359,7 @@ __host__ __device__ __forceinline__ double mean_ratio_rac(double ac, double aq, 
 __host__ __device__ __forceinline__ double mean_fixed_rac(double y, double rac) {
   const double t = fabs(y);
   const OneMinusExp o = one_minus_exp(t);
-  const double r = y == 0.0 ? 1.0 : o.em * rcp_nr(t);
+  const double r = t < 1e-290 ? 1.0 : o.em * rcp_nr(t);   // (1/t within range)
   return y > 0.0 ? r * rac : r;
 }
 

@@ -97,7 +97,8 @@ def test_square_root_and_stimulated_emission(probe):
 
 
 def test_means(probe):
-    """The group means at the host test's bounds."""
+    """The group means at the host test's bounds, and at exponents next to and
+    below the smallest number."""
     rng = np.random.default_rng(5)
     ac, aq = rng.uniform(-4, 2, N), rng.uniform(-40, 40, N)
     L = _log_spread(rng, -6, 1)
@@ -113,3 +114,5 @@ def test_means(probe):
         a, q, l = (mp.mpf(float(v)) for v in (a, q, l))
         ref = bracket(a + q + 1, l) / bracket(q + 1, l)
         assert abs(mp.mpf(float(g)) - ref) <= (32 + 4 * yy) * U * ref
+    tiny = np.array([0.0, 5e-324, -5e-324, 1e-310, -1e-310, 2.3e-308, 1e-295, -1e-200, 1e-20])
+    assert (probe(MEAN_FIXED, tiny, np.ones_like(tiny)) == 1.0).all()
