@@ -366,6 +366,8 @@ int32_t mgrhd_batch_get_item_scope(const mgrhd_batch* b);
  * 1024 cells per item) on copies of the first min(n, 1024) cells of every
  * patch, restored before each run, with HIP events on `stream`, and keeps the
  * fastest (as mgrhd_batch_set_tuning and mgrhd_batch_set_item_scope would).
+ * Candidates that cut the sample alike are timed once, and where the batch's
+ * own cells per item cut it alike too they are kept.
  * The patches' own arrays are only read.  The copies and the sample's work
  * list are allocated for the call and freed before it returns (device memory
  * of about twice the sampled state); synchronous; drops a captured graph if

@@ -357,12 +357,20 @@ static int upload_items(const std::vector<Item>& items, Item*& d) {
              ? 0 : MGRHD_E_DEVICE;
 }
 
-static int build_items(mgrhd_batch* bt) {
+static std::vector<PatchSize> patch_sizes(const mgrhd_batch* bt) {
   std::vector<PatchSize> sizes;
   for (const KArgs& a : bt->h_patches) sizes.push_back(PatchSize{a.n, a.ng});
-  CellCut cells = cut_by_cells(sizes, bt->chunk);
+  return sizes;
+}
+
+static RoundCut round_cut(const mgrhd_batch* bt, int64_t chunk) {
   const int threads[2] = {item_threads(false), item_threads(true)};
-  const RoundCut rounds = cut_by_rounds(sizes, bt->chunk, device_cus(), threads);
+  return cut_by_rounds(patch_sizes(bt), chunk, device_cus(), threads);
+}
+
+static int build_items(mgrhd_batch* bt) {
+  CellCut cells = cut_by_cells(patch_sizes(bt), bt->chunk);
+  const RoundCut rounds = round_cut(bt, bt->chunk);
   bt->n_items = (int64_t)cells.items.size();
   bt->ng_items.swap(cells.ng_items);
   bt->n_rounds = (int64_t)rounds.items.size();
@@ -799,9 +807,24 @@ int mgrhd_batch_tune(mgrhd_batch* bt, mgrhd_stream_t stream) {
     rc = MGRHD_E_DEVICE;
   float best_ms = 0.f;
   const TuneCandidate* best = nullptr;
+  int64_t best_chunk = 0;
+  // the work lists of the candidates of one workgroup per item so far: there the
+  // cells per item are a cap that a sample may never reach, and a list that was
+  // timed is not timed again
+  std::vector<RoundCut> timed;
   for (const TuneCandidate& c : kTuneCandidates) {
     if (rc) break;
     if (bt->max_groups > c.groups_per_lane * 64) continue;
+    int64_t chunk = c.chunk;
+    if (c.scope == 1 && c.groups_per_lane == 2) {
+      RoundCut cut = round_cut(&tmp, c.chunk);
+      bool seen = false;
+      for (const RoundCut& t : timed) seen = seen || t.items == cut.items;
+      if (seen) continue;
+      // nor does such a sample tell this cap from the batch's own, which then stays
+      if (round_cut(&tmp, bt->chunk).items == cut.items) chunk = bt->chunk;
+      timed.push_back(std::move(cut));
+    }
     tmp.groups_per_lane = c.groups_per_lane;
     tmp.scope = c.scope;
     tmp.blocks_per_cu = bt->blocks_per_cu;
@@ -824,6 +847,7 @@ int mgrhd_batch_tune(mgrhd_batch* bt, mgrhd_stream_t stream) {
     if (!rc && (!best || ms < best_ms)) {
       best = &c;
       best_ms = ms;
+      best_chunk = chunk;
     }
   }
   if (e0) (void)hipEventDestroy(e0);
@@ -835,7 +859,7 @@ int mgrhd_batch_tune(mgrhd_batch* bt, mgrhd_stream_t stream) {
   if (tmp.d_counter) (void)hipFree(tmp.d_counter);
   if (rc) return rc;
   if (!best) return MGRHD_E_OPTION;
-  rc = mgrhd_batch_set_tuning(bt, best->groups_per_lane, bt->blocks_per_cu, best->chunk);
+  rc = mgrhd_batch_set_tuning(bt, best->groups_per_lane, bt->blocks_per_cu, best_chunk);
   if (!rc) rc = mgrhd_batch_set_item_scope(bt, best->scope);
   return rc;
 }

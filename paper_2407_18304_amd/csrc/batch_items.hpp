@@ -16,6 +16,9 @@ struct BatchItem {
   int32_t pad;
   int64_t c0, c1;
 };
+inline bool operator==(const BatchItem& a, const BatchItem& b) {
+  return a.patch == b.patch && a.c0 == b.c0 && a.c1 == b.c1;
+}
 
 struct PatchSize {
   int64_t n;

@@ -522,3 +522,20 @@ def test_more_items_than_one_launch_holds():
     assert torch.equal(status[at], small["status"])
     status[at] = mgrhd.ST_INVALID
     assert bool((status == mgrhd.ST_INVALID).all())
+
+
+@pytest.mark.parametrize("chunk", [256, 700, 1 << 20])
+def test_autotuner_keeps_cells_per_item_it_cannot_tell(chunk):
+    """A sample whose items of one workgroup each are the same whatever their
+    cap says nothing about it: the batch's own cells per item stay."""
+    dps = synth.device_patches(W.patch_layouts(n_patches=10, seed=33, sides=(8, 12, 16),
+                                               ngs=(8, 16, 64)))
+    b = mgrhd.Batch(_patch_dicts(dps), mean_mode=1, polish=1, **_consts())
+    b.set_tuning(2, 0, chunk)
+    b.tune()
+    g, _, got = b.get_tuning()
+    if (g, b.get_item_scope()) == (2, 1):
+        assert got == chunk
+    else:
+        assert (g, b.get_item_scope(), got) in {(2, 0, 1024), (4, 0, 1024), (2, 2, 256),
+                                                (4, 2, 1024)}
