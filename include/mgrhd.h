@@ -188,9 +188,11 @@ int mgrhd_source_update(double* E_g, double* F_g, const double* rho, double* e_g
  * GPU, and most PPL-free ones, may split a cell over one lane per group unless
  * mgrhd_set_variant has been called for that count, with the same results bit
  * for bit: a cell's do not depend on how many cells a launch has): lanes per
- * cell, groups per
- * lane and the register budget, given as the minimum resident waves per SIMD
- * it is compiled for (more waves: fewer registers per lane).
+ * cell, groups per lane and the register budget, given as the minimum resident
+ * waves per SIMD it is compiled for (more waves: fewer registers per lane).
+ * Where n_groups fills two groups per lane, the budget is the library's own and
+ * the variants that differ in it alone run one kernel (four waves, or three in
+ * PPL-free with a temperature-dependent opacity).
  * mgrhd_set_variant overrides the built-in choice for n_groups (0, 0, 0
  * restores it; waves_per_simd = 0 takes the default budget of the pair);
  * variants that are not compiled, or whose lanes x groups < n_groups, return

@@ -67,8 +67,7 @@ constexpr int waves_per_simd() {
   return FULL && G == 2 && WPE > 3 ? 3 : WPE;
 }
 template <int G, int LPC, int MODE, int WPE, bool TD, bool FULL>
-__global__ __launch_bounds__((block_threads<G, FULL, MODE, TD>()),
-                             (waves_per_simd<G, MODE, WPE, TD, FULL>())) void
+__global__ __launch_bounds__((block_threads<G, FULL, MODE, TD>()), WPE) void
 k_source_update(KArgs a) {
   __shared__ BlockLds<G, LPC, block_threads<G, FULL, MODE, TD>()> lds;
   // the arguments as the device reads them in place (a is the only argument)
@@ -80,6 +79,13 @@ k_source_update(KArgs a) {
 }
 
 using KernelFn = void (*)(KArgs);
+
+// The kernel of a variant: variants that differ only in a budget that
+// waves_per_simd sets anyway share one.
+template <int G, int LPC, int MODE, int WPE, bool TD, bool FULL>
+constexpr KernelFn variant_kernel() {
+  return k_source_update<G, LPC, MODE, waves_per_simd<G, MODE, WPE, TD, FULL>(), TD, FULL>;
+}
 
 // (groups per lane, lanes per cell, minimum waves per SIMD) of every compiled
 // variant.  The first entry of each (lanes per cell, groups per lane) pair is
@@ -93,9 +99,9 @@ using KernelFn = void (*)(KArgs);
 // the three mean modes of one variant
 #define MGRHD_VARIANT_MODES(G_, LPC_, WPE_, TD_, FULL_)                            \
   {                                                                               \
-    k_source_update<G_, LPC_, MGRHD_MEAN_PC, WPE_, TD_, FULL_>,                   \
-        k_source_update<G_, LPC_, MGRHD_MEAN_PPL_FIXED, WPE_, TD_, FULL_>,        \
-        k_source_update<G_, LPC_, MGRHD_MEAN_PPL_FREE, WPE_, TD_, FULL_>          \
+    variant_kernel<G_, LPC_, MGRHD_MEAN_PC, WPE_, TD_, FULL_>(),                  \
+        variant_kernel<G_, LPC_, MGRHD_MEAN_PPL_FIXED, WPE_, TD_, FULL_>(),       \
+        variant_kernel<G_, LPC_, MGRHD_MEAN_PPL_FREE, WPE_, TD_, FULL_>()         \
   }
 
 // A kernel table: the kernel of variant k (in MGRHD_FOR_EACH_VARIANT order)
