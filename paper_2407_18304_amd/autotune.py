@@ -36,6 +36,22 @@ def save_cache(cache, path=CACHE):
         json.dump(cache, f, indent=1, sort_keys=True)
 
 
+def same_kernel(ng, a, b) -> bool:
+    """Whether two (lanes per cell, groups per lane, waves per SIMD) choices run
+    one and the same kernel: with two groups per lane that N_g fills, the
+    budget is the library's whatever is asked for."""
+    return tuple(a[:2]) == tuple(b[:2]) and (a[2] == b[2] or (a[1] == 2 and a[0] * a[1] == ng))
+
+
+def install(ng, lpc, g, wps, mode=mgrhd.MEAN_PPL_FIXED):
+    """Make a choice the library's for N_g.  Its own choice is installed by
+    removing the caller's, as a caller's holds for every launch size, while the
+    library's own splits the cells of small launches over more lanes."""
+    mgrhd.set_variant(ng, 0, 0)
+    if not same_kernel(ng, (lpc, g, wps), mgrhd.get_variant(ng, mode)):
+        mgrhd.set_variant(ng, lpc, g, wps)
+
+
 def apply_cache(path=CACHE, mode=None) -> dict:
     """Install the cached single-table choices for this GPU (for mean mode
     `mode`, or all); returns them."""
@@ -45,8 +61,8 @@ def apply_cache(path=CACHE, mode=None) -> dict:
         if mode is not None and m != mode:
             continue
         try:
-            mgrhd.set_variant(ng, rec["lanes_per_cell"], rec["groups_per_lane"],
-                              rec.get("waves_per_simd", 0))
+            install(ng, rec["lanes_per_cell"], rec["groups_per_lane"],
+                    rec.get("waves_per_simd", 0), m)
         except mgrhd.MgrhdError:
             pass
     return cache
@@ -84,6 +100,8 @@ def tune_single(dw, mode=mgrhd.MEAN_PPL_FIXED, reps=3, path=CACHE, log=print):
     for lpc, g, wps in mgrhd.variants():
         if lpc * g < dw.ng or lpc * g >= 2 * dw.ng:
             continue
+        if any(same_kernel(dw.ng, (lpc, g, wps), r[1:]) for r in results):
+            continue
         mgrhd.set_variant(dw.ng, lpc, g, wps)
         run()                    # warm up (first launch loads the code object)
         ms = _time(run, restore, reps)
@@ -91,7 +109,7 @@ def tune_single(dw, mode=mgrhd.MEAN_PPL_FIXED, reps=3, path=CACHE, log=print):
         log(f"  N_g={dw.ng} mode={mode}: {lpc} lanes x {g} groups, {wps} waves/SIMD -> {ms:.3f} ms")
     restore()
     ms, lpc, g, wps = min(results)
-    mgrhd.set_variant(dw.ng, lpc, g, wps)
+    install(dw.ng, lpc, g, wps, mode)
     cache = load_cache(path)
     ent = cache.setdefault(arch(), {}).setdefault("single", {})
     ent[f"{dw.ng}:{mode}"] = {"lanes_per_cell": lpc, "groups_per_lane": g, "waves_per_simd": wps,
@@ -119,7 +137,7 @@ def tune_batch(batch, restore, candidates=None, reps=2, path=CACHE, key="patches
         ms = _time(batch.run, restore, reps)
         results.append((ms, g, b, ch, sc))
         log(f"  batch: {g} groups/lane, {b or 'all'} blocks/CU, {ch} cells/item, "
-            f"items per {'workgroup (%d waves/SIMD)' % (4 - sc) if sc else 'wave'} -> {ms:.3f} ms")
+            f"item scope {sc} -> {ms:.3f} ms")
     restore()
     ms, g, b, ch, sc = min(results)
     batch.set_tuning(g, b, ch)
