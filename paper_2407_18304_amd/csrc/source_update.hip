@@ -146,13 +146,18 @@ static int num_cus() {
 //   84 -> 79, but 65536 x 8 122 -> 123, 8192 x 64 88 -> 97; PC 6144 x 64 77 ->
 //   74, but 7187 x 64 79 -> 84);
 // * 5 where the opacity depends on temperature, which costs two more functions
-//   per cell in every lane (20480 x 16 246 -> 223 us, but 32768 x 16 257 -> 297);
+//   per cell in every lane (pulse opacity 20480 x 16 246 -> 223 us, but 32768 x
+//   16 257 -> 297; on cells that start near equilibrium one group stays ahead,
+//   32768 x 16 217 -> 180);
 // * 8 where they leave lanes of both splits empty, since the kernels with the
-//   per-slot checks hold a third more waves at one group per lane (30011 x 11
-//   122 -> 107 us, but 125000 x 5 201 -> 213);
-// * PPL-free holds more of them still: 14 where the groups fill the lanes (43750
-//   x 16 411 -> 352 us, but 15625 x 64 322 -> 340), always where they do not
-//   (2^19 x 11 3.49 -> 3.05 ms).
+//   per-slot checks hold a third more waves at one group per lane.  3, 5, 11, 23
+//   and 51 groups, gain of one group at 4, 7, 8, 10, 12 and 16 quarters:
+//   PPL-fixed 1.03-1.18, 1.02-1.10, 1.00-1.10, 0.98-1.08, 0.94-1.01, 0.93-1.00,
+//   PC 1.01-1.15, 0.98-1.09, 0.97-1.09, 0.94-1.03, 0.94-1.02, 0.90-1.01;
+// * PPL-free holds more of them still: 14 where the groups fill the lanes (4, 16
+//   and 64 groups at 12, 14 and 16 quarters: 1.30, 1.13, 0.97; 1.22, 1.08, 1.01;
+//   1.15, 1.05, 0.95), always where they do not (5, 11 and 51 groups 1.08-1.11
+//   at 20 quarters, 1.01-1.12 at 40; 2^19 x 11 3.49 -> 3.05 ms).
 // A variant set by the caller is kept.
 static Variant* launch_variant(int ng, int mode, bool td, int64_t n) {
   Variant* v = choose_variant(ng);
