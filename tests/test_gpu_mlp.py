@@ -460,3 +460,32 @@ def test_weights_that_a_training_step_leaves(ng, rows):
     args = (dp.state, dp.tables, dp.kappa, dp.consts())
     a, b = (_warm(n, ng).guess(*args, kind=0, fused=True) for n in (net, other))
     assert bool(torch.isfinite(a).all()) and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("chunk", [1, 64, 100, 256, 1000, 1 << 20])
+def test_batched_inference_at_item_edges(chunk, kind):
+    """The inference over a batch's items, an item to a workgroup or shared by
+    several, tile by tile: every patch's guess is the one of its own launch,
+    bit for bit."""
+    ng = 4
+    net = _small_net(ng)
+    sizes = [1, 63, 64, 65, 1024, 1025, 2500]
+    edges = W.log_edges(1e-3, 1e3, ng)
+    dps = synth.device_patches([W.PatchLayout(p, n, ng, 3000 * p, edges, edges[:-1] ** -2.0,
+                                              np.full(ng, -2.0)) for p, n in enumerate(sizes)])
+    ws = _warm(net, ng)
+    patches = [dict(dp.state, edges=dp.tables["edges"], chi_lo=dp.tables["chi_lo"],
+                    alpha_chi=dp.tables["alpha"], kappa_scale=dp.kappa, dt=dp.dt, c_hat=dp.c_hat,
+                    guess=torch.full((n,) if kind else (ng + 1, n), float("nan"),
+                                     dtype=torch.float64, device="cuda"))
+               for dp, n in zip(dps, sizes)]
+    b = mgrhd.Batch(patches, c_v=1.5, guess_kind=kind, **W.UNITS["patches"])
+    b.set_tuning(2, 0, chunk)
+    b.attach_mlp(ng, ws)
+    b.infer()
+    torch.cuda.synchronize()
+    for dp, q in zip(dps, patches):
+        want = ws.guess(dp.state, dp.tables, dp.kappa, dp.consts(), kind=kind, fused=True)
+        assert torch.equal(q["guess"], want), dp.layout.n
+    b.close()
