@@ -282,6 +282,8 @@ def run_single(name, args, extra=False):
     lpc_, g_, w_ = mgrhd.get_variant(ng, args.mode)
     td = "true" if (dw.t_exp != 0.0 or dw.stim) else "false"
     full = "true" if lpc_ * g_ == ng else "false"
+    if full == "true" and g_ == 2:   # the library's own budget (waves_per_simd)
+        w_ = 3 if (td == "true" and args.mode == 2) else 4
     kname = f"k_source_update<{g_}, {lpc_}, {args.mode}, {w_}, {td}, {full}>"
     traffic = None if (warm or args.cells or args.mode != 1) else measured_traffic(name, kname)
     # headline pricing: +, -, x = 1, FMA = 2, division and square root = 1,
