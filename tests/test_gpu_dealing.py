@@ -181,3 +181,32 @@ def test_a_grid_in_pieces_gives_its_bits(ng, n, mode, td):
         got = _all(part, tables, kappa[at].contiguous(), consts, mode)
         for k in got:
             assert torch.equal(got[k], whole[k][..., at]), (k, i)
+
+
+@pytest.mark.parametrize("td", [False, True])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_every_variant_against_one_group_per_lane(mode, td):
+    """Every compiled split and register budget, at groups that fill its lanes
+    and at one fewer, twice: the same bits each time, and the cells of one
+    group per lane (which holds the fewest registers)."""
+    for lanes, groups, waves in mgrhd.variants():
+        for ng in {lanes * groups, max(lanes * groups - 1, 1)}:
+            if ng > 64:
+                continue
+            args = _cells(ng, 1500, td)
+            one = 4
+            while one < ng:
+                one *= 2
+            got = []
+            try:
+                for v in ((lanes, groups, waves), (lanes, groups, waves), (one, 1, 0)):
+                    mgrhd.set_variant(ng, *v)
+                    got.append(_all(*args, mode))
+            finally:
+                mgrhd.set_variant(ng, 0, 0)
+            what = (lanes, groups, waves, ng)
+            for k in got[0]:
+                assert torch.equal(got[0][k], got[1][k]), (*what, k)
+            assert torch.equal(got[0]["status"], got[2]["status"]), what
+            for k in KEYS:
+                _close(got[0][k], got[2][k], (*what, k))
